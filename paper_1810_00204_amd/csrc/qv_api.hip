@@ -314,7 +314,7 @@ size_t qv_filter_workspace_bytes(const qv_model *m, int32_t ntraj, int32_t T,
                                  int32_t ckpt_every) {
   if (check_model(m) != QV_OK || ntraj < 0 || T < 1 || ckpt_every < 1 || !filter_supported(m))
     return 0;
-  return filter_ws(m, ntraj, T, std::min(ckpt_every, T), filter_groups(ntraj));
+  return filter_ws(m, ntraj, T, std::min(ckpt_every, T));
 }
 
 int32_t qv_filter_nll_grad(const qv_model *m, const float *theta, const float *phi,
@@ -330,13 +330,12 @@ int32_t qv_filter_nll_grad(const qv_model *m, const float *theta, const float *p
   if ((g_slip == nullptr) != (g_flip == nullptr)) return QV_ERR_INVALID_ARG;
   if (!filter_supported(m)) return QV_ERR_UNSUPPORTED;
   const int k = std::min(ckpt_every, T);
-  const int G = filter_groups(ntraj);
-  const size_t need = filter_ws(m, ntraj, T, k, G);
+  const size_t need = filter_ws(m, ntraj, T, k);
   if (!ws_ok(ws, ws_bytes, need)) return QV_ERR_WORKSPACE;
   hipStream_t hs = (hipStream_t)stream;
   const DevModel dm = make_dev_model(m);
   st = hip_status(launch_filter(dm, theta, phi, ntraj, T, b0, b0_per_traj, acts, obs, k, nll_out,
-                                g_slip, g_flip, (char *)ws, G, hs));
+                                g_slip, g_flip, (char *)ws, hs));
   if (st != QV_OK || !check) return st;
   int32_t herr = 0;
   st = hip_status(hipMemcpyAsync(&herr, (char *)ws + need - 256, 4, hipMemcpyDeviceToHost, hs));

@@ -252,12 +252,11 @@ size_t fib_ws(const qv_model *m, int max_sweeps);
 int32_t run_model_check(const DevModel &m, const float *b0, bool check_r, char *rec,
                         hipStream_t st);
 bool filter_supported(const qv_model *m);
-int filter_groups(int ntraj);
-size_t filter_ws(const qv_model *m, int ntraj, int T, int k, int G);
+size_t filter_ws(const qv_model *m, int ntraj, int T, int k);
 hipError_t launch_filter(const DevModel &m, const float *theta, const float *phi, int ntraj,
                          int T, const float *b0, int b0_per_traj, const int32_t *acts,
                          const int32_t *obs, int k, float *nll, float *g_slip, float *g_flip,
-                         char *ws, int G, hipStream_t st);
+                         char *ws, hipStream_t st);
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
