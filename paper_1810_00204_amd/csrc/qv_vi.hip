@@ -29,6 +29,10 @@ namespace qv {
 
 constexpr int kViChunk = 32;
 constexpr int kMaxCoopGrid = 4096;   // workgroups of a one-launch solve at most
+// workgroups of a sweep launch at most: four per CU; more would only add
+// residual slots for every workgroup to read
+constexpr int kSweepGrid = 1024;
+constexpr int kMaxWaves = 16;   // wavefronts of a sweep workgroup at most
 
 // ---------------------------------------------------------------------------
 // grid barrier and the shared stopping rule
@@ -102,6 +106,30 @@ __device__ __forceinline__ double load_bits(const unsigned long long *p) {
       (long long)__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 
+// Largest of the 64 lanes' values (>= 0), in every lane, on the DPP network:
+// lane permutes through LDS would be the longest part of a small sweep.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double dpp_max(double v) {
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo =
+      (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROW_MASK, 0xF, false);
+  const uint32_t hi =
+      (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROW_MASK, 0xF, false);
+  return fmax(v, __longlong_as_double((long long)((uint64_t)hi << 32 | lo)));
+}
+__device__ __forceinline__ double wave_max(double v) {
+  v = dpp_max<0xB1, 0xF>(v);    // quad_perm [1,0,3,2]
+  v = dpp_max<0x4E, 0xF>(v);    // quad_perm [2,3,0,1]
+  v = dpp_max<0x141, 0xF>(v);   // row_half_mirror
+  v = dpp_max<0x140, 0xF>(v);   // row_mirror
+  v = dpp_max<0x142, 0xA>(v);   // row_bcast:15
+  v = dpp_max<0x143, 0xC>(v);   // row_bcast:31
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, 63);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(b >> 32), 63);
+  return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+
 // One-launch form: workgroup g's (r, max |x|) of sweep k go to slot g of the
 // sweep's parity buffer (plain coherent stores, no atomic on a shared word);
 // after the grid barrier wavefront 0 of every workgroup takes the maxima
@@ -110,21 +138,18 @@ __device__ __forceinline__ double load_bits(const unsigned long long *p) {
 // rule fires (in lane 0 of wavefront 0).
 __device__ __forceinline__ void sweep_part_store(const SweepCtl &c, int k, double r, double v,
                                                  double *red) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    r = fmax(r, __shfl_xor(r, o, kWave));
-    v = fmax(v, __shfl_xor(v, o, kWave));
-  }
+  r = wave_max(r);
+  v = wave_max(v);
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   if (lane == 0) {
     red[wave] = r;
-    red[kBlock / kWave + wave] = v;
+    red[kMaxWaves + wave] = v;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < kBlock / kWave; ++w) {
+    for (int w = 1; w < (int)blockDim.x / kWave; ++w) {
       r = fmax(r, red[w]);
-      v = fmax(v, red[kBlock / kWave + w]);
+      v = fmax(v, red[kMaxWaves + w]);
     }
     double *p = c.part + (size_t)(k & 1) * 2 * gridDim.x;
     __hip_atomic_store(p + blockIdx.x, r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -141,11 +166,8 @@ __device__ __forceinline__ int sweep_part_decide(const SweepCtl &c, int k) {
     r = fmax(r, __hip_atomic_load(p + g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     v = fmax(v, __hip_atomic_load(p + gridDim.x + g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    r = fmax(r, __shfl_xor(r, o, kWave));
-    v = fmax(v, __shfl_xor(v, o, kWave));
-  }
+  r = wave_max(r);
+  v = wave_max(v);
   if (blockIdx.x == 0 && lane == 0) {
     c.res[k] = (unsigned long long)__double_as_longlong(r);
     c.vmax[k] = (unsigned long long)__double_as_longlong(v);
@@ -153,40 +175,68 @@ __device__ __forceinline__ int sweep_part_decide(const SweepCtl &c, int k) {
   return (r == 0.0 || r <= c.tol * fmax(1.0, v)) ? 1 : 0;
 }
 
-// Stop after sweep k: r_k = 0 or r_k <= tol * max(1, max |x_k|).
-__device__ __forceinline__ bool sweep_converged(const SweepCtl &c, int k) {
-  const double r = load_bits(c.res + k), vm = load_bits(c.vmax + k);
-  return r == 0.0 || r <= c.tol * fmax(1.0, vm);
+// Per-sweep form: the workgroups' (r, max |x|) go to slots of a parity buffer
+// as above, and sweep k reads those of sweep k - 1 first.  (A max of every
+// workgroup into one word by atomics cost about 40 ns each, one after
+// another: 82 of the 123 us of a FIB sweep of 512x512.)
+
+// Workgroup maxima of sweep k's slots (g of them), in every thread.
+__device__ __forceinline__ void sweep_slots_max(const SweepCtl &c, int k, int g, double *red,
+                                                double &r, double &v) {
+  const double *p = c.part + (size_t)(k & 1) * 2 * g;
+  r = v = 0.0;
+  for (int i = threadIdx.x; i < g; i += blockDim.x) {
+    r = fmax(r, p[i]);
+    v = fmax(v, p[g + i]);
+  }
+  r = wave_max(r);
+  v = wave_max(v);
+  const int wave = threadIdx.x / kWave;
+  if ((threadIdx.x & (kWave - 1)) == 0) {
+    red[wave] = r;
+    red[kMaxWaves + wave] = v;
+  }
+  __syncthreads();
+  for (int w = 0; w < (int)blockDim.x / kWave; ++w) {
+    r = fmax(r, red[w]);
+    v = fmax(v, red[kMaxWaves + w]);
+  }
+  __syncthreads();
 }
 
-// Workgroup max of (r, v); thread 0 folds the result into sweep k's records
-// (non-negative doubles order like their bit patterns).  Ends with a barrier.
-__device__ __forceinline__ void sweep_report(double r, double v, unsigned long long *res,
-                                             unsigned long long *vmax, int k, double *red) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    r = fmax(r, __shfl_xor(r, o, kWave));
-    v = fmax(v, __shfl_xor(v, o, kWave));
+// Start of sweep k: records sweep k - 1's residual; if its rule fired
+// (r = 0 or r <= tol * max(1, max |x|)), hands its slots on to the next sweep,
+// so that all later ones stop too, and returns true.
+__device__ __forceinline__ bool sweep_stopped(const SweepCtl &c, int k, double *red) {
+  if (k <= 1) return false;
+  const int g = gridDim.x;
+  double r, v;
+  sweep_slots_max(c, k - 1, g, red, r, v);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    c.res[k - 1] = (unsigned long long)__double_as_longlong(r);
+    c.vmax[k - 1] = (unsigned long long)__double_as_longlong(v);
   }
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  if (lane == 0) {
-    red[wave] = r;
-    red[kBlock / kWave + wave] = v;
+  if (!(r == 0.0 || r <= c.tol * fmax(1.0, v))) return false;
+  if (threadIdx.x < 2) {
+    const size_t at = (size_t)threadIdx.x * g + blockIdx.x;
+    c.part[(size_t)(k & 1) * 2 * g + at] = c.part[(size_t)((k - 1) & 1) * 2 * g + at];
   }
-  __syncthreads();
+  return true;
+}
+
+// The residual of the last sweep launched (k, of g workgroups).
+__global__ __launch_bounds__(kBlock) void k_sweep_close(SweepCtl c, int k, int g) {
+  __shared__ double red[2 * kMaxWaves];
+  double r, v;
+  sweep_slots_max(c, k, g, red, r, v);
   if (threadIdx.x == 0) {
-    for (int w = 1; w < kBlock / kWave; ++w) {
-      r = fmax(r, red[w]);
-      v = fmax(v, red[kBlock / kWave + w]);
-    }
-    atomicMax(&res[k], (unsigned long long)__double_as_longlong(r));
-    atomicMax(&vmax[k], (unsigned long long)__double_as_longlong(v));
+    c.res[k] = (unsigned long long)__double_as_longlong(r);
+    c.vmax[k] = (unsigned long long)__double_as_longlong(v);
   }
-  __syncthreads();
 }
 
 __global__ void k_sweep_fill(unsigned long long *res, unsigned long long *vmax, int n,
-                             unsigned long long *bar, float *x0, long long nx) {
+                             unsigned long long *bar, float *x0, float *x1, long long nx) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) {
     res[i] = 0ull;
@@ -196,7 +246,10 @@ __global__ void k_sweep_fill(unsigned long long *res, unsigned long long *vmax, 
     bar[0] = 0ull;   // barrier counter
     bar[2] = 0ull;   // sweep count and abort flag
   }
-  if (i < nx) x0[i] = 0.f;
+  if (i < nx) {
+    x0[i] = 0.f;
+    x1[i] = 0.f;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -323,7 +376,7 @@ __global__ __launch_bounds__(kBlock) void k_vi_coop(DevModel m, const uint32_t *
                                                     float *V0, float *V1, float *Q,
                                                     SweepCtl c) {
   extern __shared__ float smem[];
-  __shared__ double red[2 * kBlock / kWave];
+  __shared__ double red[2 * kMaxWaves];
   __shared__ int s_stop;
   if (threadIdx.x == 0) s_stop = 0;
   int kend = c.max_sweeps;
@@ -360,15 +413,16 @@ __global__ __launch_bounds__(kBlock) void k_vi_coop(DevModel m, const uint32_t *
 // Per-sweep form: sweep k >= 1, V_k from V_{k-1}; does nothing once the
 // rule has fired at an earlier sweep.
 __global__ __launch_bounds__(kBlock) void k_vi_sweep(DevModel m, const uint32_t *sig,
-                                                     const float *staytab, int TH,
+                                                     const float *staytab, int TH, int tiles,
                                                      const float *Vin, float *Vout, int k,
                                                      SweepCtl c) {
-  if (k > 1 && sweep_converged(c, k - 1)) return;
   extern __shared__ float smem[];
-  __shared__ double red[2 * kBlock / kWave];
+  __shared__ double red[2 * kMaxWaves];
+  if (sweep_stopped(c, k, red)) return;
   double r = 0.0, vm = 0.0;
-  vi_band<false>(m, sig, staytab, TH, blockIdx.x, Vin, Vout, smem, r, vm);
-  sweep_report(r, vm, c.res, c.vmax, k, red);
+  for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x)
+    vi_band<false>(m, sig, staytab, TH, tile, Vin, Vout, smem, r, vm);
+  sweep_part_store(c, k, r, vm, red);
 }
 
 // Q_k(s,.) from V_{k-1}, the Q-values of the last sweep (same arithmetic).
@@ -383,109 +437,434 @@ __global__ __launch_bounds__(kBlock) void k_vi_q(DevModel m, const uint32_t *sig
 // fast informed bound
 // ---------------------------------------------------------------------------
 
-// The FIB right-hand side at free cell x for every action (AM >= A columns,
-// rows of the alpha tables have A entries).  The successors of x are its
-// neighbours k != 4 that a move enters (sig bits) and x itself, which takes
-// the stay mass: T(x,a,x + d_k) = T'(a,k), T(x,a,x) = stay(x,a).  With
-// C[zw][w] the wall-reading likelihood (ctab) and lambda(x') = 1 - rho on a
-// landmark cell, else 1, the sum over z splits into
+// What a sweep needs to know of a free cell x, gathered once per solve:
+//   bits 0..35  wall readings of the successors k = 0..8 (4 bits each; of x
+//               itself where move k fails),
+//   bits 36..43 the moves that succeed (order of the map signature),
+//   bits 44..52 successor k carries a landmark,
+//   bits 53..56 the wall bits in which the successors' readings differ,
+//   bit  57     the goal.
+// fib_terms of a record: the number of its differing bits.
+constexpr int kFibOut = 36, kFibLm = 44, kFibDiff = 53, kFibGoal = 57;
+constexpr int kFibClasses = 5;
+
+__device__ __forceinline__ uint64_t fib_record(const DevModel &m, const uint32_t *sig, int x,
+                                               uint32_t sg) {
+  uint64_t rec = (uint64_t)sig_out8(sg) << kFibOut;
+  if (sg & kSigGoal) return rec | (1ull << kFibGoal);   // absorbing: only itself
+  uint32_t all1 = 15u, any1 = 0u;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    const bool ok = k == 4 || ((sg >> (k < 4 ? k : k - 1)) & 1u);
+    const uint32_t st = sig[ok ? x + (k / 3 - 1) * m.W + (k % 3 - 1) : x];
+    const uint32_t w = sig_wall(st), lm = sig_lm(st);
+    all1 &= w;
+    any1 |= w;
+    rec |= (uint64_t)w << (4 * k);
+    if (ok && lm != 0u && lm <= (uint32_t)m.L) rec |= 1ull << (kFibLm + k);
+  }
+  return rec | (uint64_t)(any1 & ~all1) << kFibDiff;
+}
+
+__device__ __forceinline__ int fib_terms(uint64_t rec) {
+  return __builtin_popcount((uint32_t)(rec >> kFibDiff) & 15u);
+}
+
+// The free cells in order of the number of differing wall bits, most first
+// (the long work starts early), by index within a class: count per block and
+// class, scan, scatter.  ctl[0] is the number of free cells.
+__global__ __launch_bounds__(kBlock) void k_fib_count(DevModel m, const uint32_t *sig,
+                                                      int32_t *counts) {
+  __shared__ int32_t n[kFibClasses];
+  if (threadIdx.x < kFibClasses) n[threadIdx.x] = 0;
+  __syncthreads();
+  const int x = blockIdx.x * kBlock + threadIdx.x;
+  if (x < m.S) {
+    const uint32_t sg = sig[x];
+    if (sg & kSigFree) atomicAdd(&n[kFibClasses - 1 - fib_terms(fib_record(m, sig, x, sg))], 1);
+  }
+  __syncthreads();
+  if (threadIdx.x < kFibClasses) counts[threadIdx.x * gridDim.x + blockIdx.x] = n[threadIdx.x];
+}
+
+__global__ __launch_bounds__(1024) void k_fib_scan(int32_t *counts, int n, int32_t *ctl) {
+  __shared__ int32_t sums[16];
+  __shared__ int32_t base;
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  if (threadIdx.x == 0) base = 0;
+  __syncthreads();
+  for (int i0 = 0; i0 < n; i0 += 1024) {
+    const int i = i0 + threadIdx.x;
+    const int v = i < n ? counts[i] : 0;
+    const int incl = wave_scan_incl(v);
+    if (lane == kWave - 1) sums[wave] = incl;
+    __syncthreads();
+    int before = base;
+    for (int w = 0; w < wave; ++w) before += sums[w];
+    if (i < n) counts[i] = before + incl - v;
+    __syncthreads();
+    if (threadIdx.x == 1023) base = before + incl;
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) ctl[0] = base;
+}
+
+__global__ __launch_bounds__(kBlock) void k_fib_scatter(DevModel m, const uint32_t *sig,
+                                                        const int32_t *counts, int32_t *cells,
+                                                        uint64_t *recs) {
+  __shared__ int32_t n[kBlock / kWave][kFibClasses];
+  const int x = blockIdx.x * kBlock + threadIdx.x;
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const uint32_t sg = x < m.S ? sig[x] : 0u;
+  const bool free = (sg & kSigFree) != 0u;
+  const uint64_t rec = free ? fib_record(m, sig, x, sg) : 0ull;
+  const int cls = free ? kFibClasses - 1 - fib_terms(rec) : kFibClasses;
+  int rank = 0;
+  for (int c = 0; c < kFibClasses; ++c) {
+    const uint64_t in = __ballot(cls == c);
+    if (cls == c) rank = __popcll(in & ((1ull << lane) - 1ull));
+    if (lane == 0) n[wave][c] = __popcll(in);
+  }
+  __syncthreads();
+  if (!free) return;
+  int at = counts[cls * gridDim.x + blockIdx.x] + rank;
+  for (int w = 0; w < wave; ++w) at += n[w][cls];
+  cells[at] = x;
+  recs[at] = rec;
+}
+
+// The slip table in a register per lane: lane 3 a + k % 3 of register k / 3
+// holds T'(a,k), so that an entry is one lane read and not a scalar load that
+// the next instruction waits for.
+struct SlipLanes {
+  float v[3];
+  uint64_t nz[3];   // lanes that are not 0
+  __device__ __forceinline__ explicit SlipLanes(const DevModel &m) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const bool has = lane < 3 * m.A;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      v[i] = has ? m.slip[lane / 3 * 9 + 3 * i + lane % 3] : 0.f;
+      nz[i] = __ballot(v[i] != 0.f);
+    }
+  }
+  __device__ __forceinline__ bool moves(int a, int k) const {
+    return (nz[k / 3] >> (3 * a + k % 3)) & 1ull;
+  }
+  __device__ __forceinline__ float at(int a, int k) const {
+    return __int_as_float(
+        __builtin_amdgcn_readlane(__float_as_int(v[k / 3]), 3 * a + k % 3));
+  }
+};
+
+// The FIB right-hand side.  The successors of a free cell x are its neighbours
+// k != 4 that a move enters and x itself, which takes the stay mass:
+// T(x,a,x + d_k) = T'(a,k), T(x,a,x) = stay(x,a).  With C[zw][w] the
+// wall-reading likelihood and lambda(x') = 1 - rho on a landmark cell, else 1,
+// the sum over z splits into
 //   zl = 0:  sum_zw max_a' sum_k C[zw][w(x_k)] lambda(x_k) T_k(a) alpha^a'(x_k),
 //   zl = l:  rho T_k(a) max_a' alpha^a'(x_k) for the successor x_k that is
 //            landmark l (only it can report l, and sum_zw C[zw][w] = 1).
-// The goal is absorbing: its right-hand side is R + gamma max_a' alpha^a'(goal).
+// C is a product over the wall bits.  The factors of a bit in which all
+// successors agree leave the max and sum to 1 over that bit of zw, so zw runs
+// only over the bits in which they differ: 2^bits terms instead of 16, one
+// in the open.  Moves of probability 0 are left out: of nine, the slip tables
+// in use make three or four.  The goal is absorbing: its right-hand side is
+// R + gamma max_a' alpha^a'(goal).
+//
+// A workgroup of one wavefront per action takes 64 cells at a time: the
+// wavefronts stage the nine successors' rows and the reward row in LDS (zero
+// where a move fails, scaled by lambda on a landmark), then each forms its
+// action's value from the rows its moves need, held in registers.  Bound by
+// the vector ALU and the latency of the row loads; one thread per cell with
+// all rows and actions took 160 VGPRs, three wavefronts per SIMD, and left
+// both exposed.  Measured, 512x512, a sweep: 123 us before (16 terms of nine moves for
+// every cell, and the residual's atomics), 24.8 now.
+template <int AM>
+struct FibShared {
+  static constexpr int Q = AM / 4, E = AM % 4;   // a row: Q 4-vectors and E (0 or 1) values
+  float4 q[10][Q][kWave];                        // successors 0..8, reward row 9
+  float e[E ? 10 : 1][E ? kWave : 1];
+  float mk[9][kWave];                            // rho max_a' of a landmark's row, else 0
+  float out[AM * (kWave + 1)];
+  float stay[AM * 256];
+  float ctab[256];
+  int cell[kWave];
+};
+
+// Row t of an alpha or reward table into registers.
 template <int AM, bool COH>
-__device__ __forceinline__ void fib_cell(const DevModel &m, const uint32_t *sig,
-                                         const float *staytab, const float *al,
-                                         const float *ctab, int x, uint32_t sg,
-                                         float (&out)[AM]) {
-  const int A = m.A, W = m.W, L = m.L;
-  const float rho = m.lm_p;
-  if (sg & kSigGoal) {
-    float best = -INFINITY;
+__device__ __forceinline__ void fib_row(const float *al, int t, int A, bool vec, float (&v)[AM]) {
+  if constexpr (!COH && AM % 4 == 0) {
+    if (vec) {   // rows of AM values, 16-byte aligned
+      const float4 *q = reinterpret_cast<const float4 *>(al + (size_t)t * AM);
 #pragma unroll
-    for (int ap = 0; ap < AM; ++ap)
-      if (ap < A) best = fmaxf(best, ld_val<COH>(al + (size_t)x * A + ap));
-#pragma unroll
-    for (int a = 0; a < AM; ++a)
-      out[a] = a < A ? fmaf(m.gamma, best, m.R[(size_t)x * A + a]) : 0.f;
-    return;
-  }
-  // the successors' alpha rows (zero where the move fails), wall readings
-  // and landmark factors; loads go out together at valid addresses
-  float v[9][AM];
-  uint32_t wk[9];
-  float lam[9];
-  bool lmk[9];
-#pragma unroll
-  for (int k = 0; k < 9; ++k) {
-    const bool ok = (k == 4) || ((sg >> (k < 4 ? k : k - 1)) & 1u);
-    const int t = ok ? x + (k / 3 - 1) * W + (k % 3 - 1) : x;
-    const uint32_t st = sig[t];
-    const uint32_t lm = sig_lm(st);
-    wk[k] = sig_wall(st);
-    lmk[k] = ok && lm != 0u && lm <= (uint32_t)L;
-    lam[k] = lmk[k] ? 1.f - rho : 1.f;
-#pragma unroll
-    for (int ap = 0; ap < AM; ++ap) {
-      const float av = ld_val<COH>(al + (size_t)t * A + (ap < A ? ap : 0));
-      v[k][ap] = (ok && ap < A) ? av : 0.f;
-    }
-  }
-  float acc[AM], stay[AM];
-  const int pat = (int)sig_out8(sg);
-#pragma unroll
-  for (int a = 0; a < AM; ++a) {
-    acc[a] = 0.f;
-    stay[a] = staytab[(a < A ? a : 0) * 256 + pat];
-  }
-  for (int zw = 0; zw < 16; ++zw) {
-    float cw[9];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) cw[k] = ctab[zw * 16 + wk[k]] * lam[k];
-#pragma unroll
-    for (int a = 0; a < AM; ++a) {
-      if (a >= A) continue;
-      float g[9];
-#pragma unroll
-      for (int k = 0; k < 9; ++k)
-        g[k] = cw[k] * (k == 4 ? stay[a] : m.slip[a * 9 + k]);
-      float best = -INFINITY;
-#pragma unroll
-      for (int ap = 0; ap < AM; ++ap) {
-        if (ap >= A) continue;
-        float s = g[0] * v[0][ap];
-#pragma unroll
-        for (int k = 1; k < 9; ++k) s = fmaf(g[k], v[k][ap], s);
-        best = fmaxf(best, s);
+      for (int i = 0; i < AM / 4; ++i) {
+        const float4 f = q[i];
+        v[4 * i] = f.x;
+        v[4 * i + 1] = f.y;
+        v[4 * i + 2] = f.z;
+        v[4 * i + 3] = f.w;
       }
-      acc[a] += best;
+      return;
     }
   }
-  // landmark observations of the successors
+  // (columns beyond A repeat column 0)
 #pragma unroll
-  for (int k = 0; k < 9; ++k) {
-    if (!lmk[k]) continue;
-    float mk = -INFINITY;
+  for (int ap = 0; ap < AM; ++ap) v[ap] = ld_val<COH>(al + (size_t)t * A + (ap < A ? ap : 0));
+}
+
+template <int AM>
+__device__ __forceinline__ float fib_row_max(const float (&v)[AM]) {
+  float mx = v[0];
 #pragma unroll
-    for (int ap = 0; ap < AM; ++ap)
-      if (ap < A) mk = fmaxf(mk, v[k][ap]);
+  for (int ap = 1; ap < AM; ++ap) mx = fmaxf(mx, v[ap]);
+  return mx;
+}
+
+template <int AM>
+__device__ __forceinline__ void fib_put(FibShared<AM> &sh, int k, const float (&v)[AM]) {
+  const int lane = threadIdx.x & (kWave - 1);
 #pragma unroll
-    for (int a = 0; a < AM; ++a) {
-      if (a >= A) continue;
-      const float tk = k == 4 ? stay[a] : m.slip[a * 9 + k];
-      acc[a] = fmaf(rho * tk, mk, acc[a]);
+  for (int i = 0; i < AM / 4; ++i)
+    sh.q[k][i][lane] = make_float4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
+  if constexpr (AM % 4 != 0) sh.e[k][lane] = v[AM - 1];
+}
+
+template <int AM>
+__device__ __forceinline__ void fib_get(const FibShared<AM> &sh, int k, float (&v)[AM]) {
+  const int lane = threadIdx.x & (kWave - 1);
+#pragma unroll
+  for (int i = 0; i < AM / 4; ++i) {
+    const float4 f = sh.q[k][i][lane];
+    v[4 * i] = f.x;
+    v[4 * i + 1] = f.y;
+    v[4 * i + 2] = f.z;
+    v[4 * i + 3] = f.w;
+  }
+  if constexpr (AM % 4 != 0) v[AM - 1] = sh.e[k][lane];
+}
+
+// Entry a (uniform) of a staged row.
+template <int AM>
+__device__ __forceinline__ float fib_get1(const FibShared<AM> &sh, int k, int a) {
+  const int lane = threadIdx.x & (kWave - 1);
+  if (AM % 4 != 0 && a == AM - 1) return sh.e[k][lane];
+  return reinterpret_cast<const float *>(&sh.q[k][a / 4][lane])[a % 4];
+}
+
+// The sorted cells of a FIB solve in its workspace.
+struct FibCells {
+  int32_t *cells, *counts, *ctl;   // [S], [classes][blocks], number of free cells
+  uint64_t *recs;                  // [S]
+  int nfree;
+};
+
+// The moves of an action that have a probability, without k = 4 (uniform).
+template <int NJ>
+struct FibMoves {
+  int k[NJ], n;
+  float T[NJ];
+  __device__ __forceinline__ FibMoves(const SlipLanes &sl, int a) : n(0) {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      k[j] = 4;
+      T[j] = 0.f;
+    }
+#pragma unroll
+    for (int kk = 0; kk < 9; ++kk) {
+      if (kk == 4 || !sl.moves(a, kk)) continue;
+      const float t = sl.at(a, kk);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+        if (j == n) {
+          k[j] = kk;
+          T[j] = t;
+        }
+      ++n;
     }
   }
+};
+
+// Tables of a launch, once per workgroup: the stay entries, and entry D*16 +
+// mis of ctab, the product over the wall bits j of D of (bit j of mis set ?
+// f_j : 1 - f_j).
+template <int AM>
+__device__ __forceinline__ void fib_tables(const DevModel &m, const float *staytab,
+                                           FibShared<AM> &sh) {
+  for (int i = threadIdx.x; i < m.A * 256; i += blockDim.x) sh.stay[i] = staytab[i];
+  for (int i = threadIdx.x; i < 256; i += blockDim.x) {
+    const uint32_t D = (uint32_t)i >> 4, mis = (uint32_t)i & 15u;
+    float c = 1.f;
 #pragma unroll
-  for (int a = 0; a < AM; ++a)
-    out[a] = a < A ? fmaf(m.gamma, acc[a], m.R[(size_t)x * A + a]) : 0.f;
+    for (int j = 0; j < 4; ++j)
+      if ((D >> j) & 1u) c *= ((mis >> j) & 1u) ? m.flip[j] : 1.f - m.flip[j];
+    sh.ctab[i] = c;
+  }
+}
+
+// The rows that a wavefront stages for a group of 64 cells, in flight while
+// the group before is computed.
+template <int AM>
+struct FibRows {
+  static constexpr int N = AM == 4 ? 10 : 2;   // rows k = a, a + A, .. < 10 (A > 4: two at most)
+  float v[N][AM];
+  int x;
+  uint64_t rec;
+  bool has;
+};
+
+template <int AM>
+__device__ __forceinline__ void fib_cells_load(const FibCells &fc, int g, FibRows<AM> &f) {
+  const int j = g * kWave + (int)(threadIdx.x & (kWave - 1));
+  f.has = j < fc.nfree;
+  f.x = f.has ? fc.cells[j] : 0;
+  f.rec = f.has ? fc.recs[j] : 0ull;
+}
+
+template <int AM, bool COH>
+__device__ __forceinline__ void fib_rows_load(const DevModel &m, int a, const float *ain, bool vec,
+                                              bool rvec, FibRows<AM> &f) {
+  const int A = m.A, W = m.W;
+  const uint32_t out8 = (uint32_t)(f.rec >> kFibOut) & 255u;
+#pragma unroll
+  for (int i = 0; i < FibRows<AM>::N; ++i) {
+    const int k = a + i * A;
+    if (k > 9) continue;
+    if (k == 9) {
+      fib_row<AM, false>(m.R, f.x, A, rvec, f.v[i]);
+    } else {
+      const bool ok = k == 4 || ((out8 >> (k < 4 ? k : k - 1)) & 1u);
+      fib_row<AM, COH>(ain, ok ? f.x + (k / 3 - 1) * W + (k % 3 - 1) : f.x, A, vec, f.v[i]);
+    }
+  }
+}
+
+template <int AM>
+__device__ __forceinline__ void fib_rows_put(const DevModel &m, int a, FibRows<AM> &f,
+                                             FibShared<AM> &sh) {
+  const int A = m.A, lane = threadIdx.x & (kWave - 1);
+  const float rho = m.lm_p;
+  const uint32_t out8 = (uint32_t)(f.rec >> kFibOut) & 255u;
+  if (a == 0) sh.cell[lane] = f.has ? f.x : -1;
+#pragma unroll
+  for (int i = 0; i < FibRows<AM>::N; ++i) {
+    const int k = a + i * A;
+    if (k > 9) continue;
+    if (k < 9) {
+      const bool ok = f.has && (k == 4 || ((out8 >> (k < 4 ? k : k - 1)) & 1u));
+      float mk = 0.f, s = 1.f;
+      if ((f.rec >> (kFibLm + k)) & 1ull) {
+        mk = rho * fib_row_max<AM>(f.v[i]);
+        s = 1.f - rho;
+      }
+      // (selected, not multiplied: a failed move's row may hold anything)
+#pragma unroll
+      for (int ap = 0; ap < AM; ++ap) f.v[i][ap] = ok ? s * f.v[i][ap] : 0.f;
+      sh.mk[k][lane] = mk;
+    }
+    fib_put<AM>(sh, k, f.v[i]);
+  }
+}
+
+// One FIB sweep over the sorted free cells (blocked cells keep their 0);
+// `f` holds the workgroup's first group of cells.
+template <int AM, int NJ, bool COH>
+__device__ __forceinline__ void fib_pass(const DevModel &m, const FibCells &fc,
+                                         const FibMoves<NJ> &mv, FibShared<AM> &sh, int a,
+                                         const float *ain, float *aout, bool vec, bool rvec,
+                                         FibRows<AM> f, double &r, double &vm) {
+  const int A = m.A, lane = threadIdx.x & (kWave - 1);
+  const int groups = (fc.nfree + kWave - 1) / kWave;
+  for (int g = blockIdx.x; g < groups; g += gridDim.x) {
+    const int x = f.x;
+    const uint64_t rec = f.rec;
+    const bool has = f.has;
+    const uint32_t out8 = (uint32_t)(rec >> kFibOut) & 255u;
+    fib_rows_put<AM>(m, a, f, sh);
+    const bool lms = __ballot(((uint32_t)(rec >> kFibLm) & 511u) != 0u) != 0ull;
+    const bool more = g + (int)gridDim.x < groups;
+    if (more) fib_cells_load<AM>(fc, g + gridDim.x, f);
+    __syncthreads();
+    // ---- this wavefront's action
+    {
+      float v4[AM], v[NJ][AM];
+      fib_get<AM>(sh, 4, v4);
+      const bool lm4 = (rec >> (kFibLm + 4)) & 1ull;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+        if (j < mv.n) fib_get<AM>(sh, mv.k[j], v[j]);
+      const float R = fib_get1<AM>(sh, 9, a), stay = sh.stay[a * 256 + (int)out8];
+      if (more) fib_rows_load<AM, COH>(m, a, ain, vec, rvec, f);
+      float acc = 0.f;
+      if (lms) {
+        acc = stay * sh.mk[4][lane];
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+          if (j < mv.n) acc = fmaf(mv.T[j], sh.mk[mv.k[j]][lane], acc);
+      }
+      const uint32_t diff = (uint32_t)(rec >> kFibDiff) & 15u;
+      if (__ballot(diff != 0u) == 0ull) {   // one term, C = 1
+        float s[AM];
+#pragma unroll
+        for (int ap = 0; ap < AM; ++ap) s[ap] = stay * v4[ap];
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+          if (j < mv.n) {
+#pragma unroll
+            for (int ap = 0; ap < AM; ++ap) s[ap] = fmaf(mv.T[j], v[j][ap], s[ap]);
+          }
+        acc += fib_row_max<AM>(s);
+      } else {
+        // byte offsets of the successors' entries of ctab row `diff` for zw = 0
+        const uint32_t row = diff << 6;
+        const uint32_t e4 = row | (((uint32_t)(rec >> 16) & diff) << 2);
+        uint32_t e[NJ];
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) e[j] = row | (((uint32_t)(rec >> (4 * mv.k[j])) & diff) << 2);
+        const char *ct = reinterpret_cast<const char *>(sh.ctab);
+        uint32_t zw = 0u;   // (its bits shifted by two, as the offsets)
+        do {
+          const float g4 = *reinterpret_cast<const float *>(ct + (e4 ^ zw)) * stay;
+          float s[AM];
+#pragma unroll
+          for (int ap = 0; ap < AM; ++ap) s[ap] = g4 * v4[ap];
+#pragma unroll
+          for (int j = 0; j < NJ; ++j)
+            if (j < mv.n) {
+              const float gj = *reinterpret_cast<const float *>(ct + (e[j] ^ zw)) * mv.T[j];
+#pragma unroll
+              for (int ap = 0; ap < AM; ++ap) s[ap] = fmaf(gj, v[j][ap], s[ap]);
+            }
+          acc += fib_row_max<AM>(s);
+          zw = (zw - (diff << 2)) & (diff << 2);   // the next subset of the differing bits
+        } while (zw != 0u);
+      }
+      // the old value: row 4's entry, before lambda
+      float old = fib_get1<AM>(sh, 4, a);
+      float o = fmaf(m.gamma, acc, R);
+      if ((rec >> kFibGoal) & 1ull) o = fmaf(m.gamma, fib_row_max<AM>(v4), R);
+      if (lm4) old = ld_val<COH>(ain + (size_t)x * A + a);
+      if (has) {
+        r = fmax(r, fabs((double)o - (double)old));
+        vm = fmax(vm, fabs((double)o));
+      }
+      sh.out[a * (kWave + 1) + lane] = o;
+    }
+    __syncthreads();
+    // ---- a value per thread, rows contiguous
+    const int c = threadIdx.x / A, ca = threadIdx.x - c * A, xc = sh.cell[c];
+    if (xc >= 0) st_val<COH>(aout + (size_t)xc * A + ca, sh.out[ca * (kWave + 1) + c]);
+    if (more) __syncthreads();
+  }
 }
 
 // The blind-policy right-hand side at free cell x for every action: each
 // action's own vector, alpha^a(x) = R(x,a) + gamma sum_x' T(x,a,x') alpha^a(x')
 // (no max over actions: the value of taking a forever, a lower bound).
 template <int AM, bool COH>
-__device__ __forceinline__ void blind_cell(const DevModel &m, const uint32_t *sig,
+__device__ __forceinline__ void blind_cell(const DevModel &m, const SlipLanes &sl,
+                                           const uint32_t *sig,
                                            const float *staytab, const float *al, int x,
                                            uint32_t sg, float (&out)[AM]) {
   const int A = m.A, W = m.W;
@@ -509,7 +888,7 @@ __device__ __forceinline__ void blind_cell(const DevModel &m, const uint32_t *si
     for (int a = 0; a < AM; ++a) {
       if (a >= A) continue;
       const float av = ld_val<COH>(al + (size_t)t * A + a);
-      const float tk = k == 4 ? staytab[a * 256 + pat] : m.slip[a * 9 + k];
+      const float tk = k == 4 ? staytab[a * 256 + pat] : sl.at(a, k);
       acc[a] = fmaf(tk, ok ? av : 0.f, acc[a]);
     }
   }
@@ -518,27 +897,18 @@ __device__ __forceinline__ void blind_cell(const DevModel &m, const uint32_t *si
     out[a] = a < A ? fmaf(m.gamma, acc[a], m.R[(size_t)x * A + a]) : 0.f;
 }
 
-// C[zw][w] = prod_j (bit j of zw ^ w set ? f_j : 1 - f_j) into LDS.
-__device__ __forceinline__ void fib_ctab(const DevModel &m, float *ctab) {
-  if (threadIdx.x < 256) ctab[threadIdx.x] = wall_lik(m.flip, threadIdx.x >> 4, threadIdx.x & 15u);
-  __syncthreads();
-}
-
-// One sweep over the cells i = blockIdx.x * kBlock + threadIdx.x + j * stride.
-template <int AM, bool COH, int OP>
-__device__ __forceinline__ void fib_pass(const DevModel &m, const uint32_t *sig,
-                                         const float *staytab, const float *ain, float *aout,
-                                         const float *ctab, long long stride, double &r,
-                                         double &vm) {
+// One blind-bound sweep over the cells blockIdx.x * kBlock + threadIdx.x + j * stride.
+template <int AM, bool COH>
+__device__ __forceinline__ void blind_pass(const DevModel &m, const SlipLanes &sl,
+                                           const uint32_t *sig,
+                                           const float *staytab, const float *ain, float *aout,
+                                           long long stride, double &r, double &vm) {
   const int A = m.A;
   for (long long x = (long long)blockIdx.x * kBlock + threadIdx.x; x < m.S; x += stride) {
     const uint32_t sg = sig[x];
     float o[AM];
     if (sg & kSigFree) {
-      if constexpr (OP == 0)
-        fib_cell<AM, COH>(m, sig, staytab, ain, ctab, (int)x, sg, o);
-      else
-        blind_cell<AM, COH>(m, sig, staytab, ain, (int)x, sg, o);
+      blind_cell<AM, COH>(m, sl, sig, staytab, ain, (int)x, sg, o);
 #pragma unroll
       for (int a = 0; a < AM; ++a) {
         if (a >= A) continue;
@@ -555,42 +925,36 @@ __device__ __forceinline__ void fib_pass(const DevModel &m, const uint32_t *sig,
   }
 }
 
-// Every FIB sweep in one launch (cooperative).  al[0] holds alpha_0 = 0;
-// sweep k writes alpha_k into al[k & 1]; the last one is copied to out.
-template <int AM, int OP>
-__global__ __launch_bounds__(kBlock) void k_fib_coop(DevModel m, const uint32_t *sig,
-                                                     const float *staytab, float *al0,
-                                                     float *al1, float *out, SweepCtl c) {
-  __shared__ float ctab[256];
-  __shared__ double red[2 * kBlock / kWave];
-  __shared__ int s_stop;
-  if (threadIdx.x == 0) s_stop = 0;
-  fib_ctab(m, ctab);
-  const long long stride = (long long)gridDim.x * kBlock;
-  int kend = c.max_sweeps;
+// Sweeps k = 1, 2, .. of a cooperative solve: SWEEP(k, in, out, r, vm) does
+// one; x0 holds 0, sweep k writes x[k & 1].  Returns the last sweep, or 0 if a
+// barrier wait gave up.
+template <class SWEEP>
+__device__ __forceinline__ int coop_sweeps(const SweepCtl &c, float *x0, float *x1, double *red,
+                                           int *s_stop, SWEEP sweep) {
+  if (threadIdx.x == 0) *s_stop = 0;
   for (int k = 1; k <= c.max_sweeps; ++k) {
-    const float *ain = (k & 1) ? al0 : al1;
-    float *aout = (k & 1) ? al1 : al0;
     double r = 0.0, vm = 0.0;
-    fib_pass<AM, true, OP>(m, sig, staytab, ain, aout, ctab, stride, r, vm);
+    sweep((k & 1) ? x0 : x1, (k & 1) ? x1 : x0, r, vm);
     sweep_part_store(c, k, r, vm, red);
     grid_sync(c.bar, (unsigned long long)k * gridDim.x, c.abort);
     if (threadIdx.x < kWave) {
       const int conv = sweep_part_decide(c, k);
       if (threadIdx.x == 0)
-        s_stop = __hip_atomic_load(c.abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? 2
-                                                                                        : conv;
+        *s_stop = __hip_atomic_load(c.abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? 2
+                                                                                         : conv;
     }
     __syncthreads();
-    if (s_stop) {
-      kend = k;
-      break;
-    }
+    if (*s_stop) return *s_stop == 2 ? 0 : k;   // the same decision in every workgroup
   }
-  if (s_stop == 2) return;
-  const float *last = (kend & 1) ? al1 : al0;
-  const long long n = (long long)m.S * m.A;
-  for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < n; i += stride)
+  return c.max_sweeps;
+}
+
+// The last sweep's values to `out`, its number and residual to the host's words.
+__device__ __forceinline__ void coop_result(const SweepCtl &c, int kend, const float *x0,
+                                            const float *x1, float *out, long long n) {
+  const float *last = (kend & 1) ? x1 : x0;
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (long long)gridDim.x * blockDim.x)
     out[i] = ld_val<true>(last + i);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     *c.out_k = kend;
@@ -598,19 +962,74 @@ __global__ __launch_bounds__(kBlock) void k_fib_coop(DevModel m, const uint32_t 
   }
 }
 
-// Per-sweep form of FIB sweep k (nothing once the rule has fired).
-template <int AM, int OP>
-__global__ __launch_bounds__(kBlock) void k_fib_sweep(DevModel m, const uint32_t *sig,
-                                                      const float *staytab, const float *ain,
-                                                      float *aout, int k, SweepCtl c) {
-  if (k > 1 && sweep_converged(c, k - 1)) return;
-  __shared__ float ctab[256];
-  __shared__ double red[2 * kBlock / kWave];
-  fib_ctab(m, ctab);
+// Every FIB sweep in one launch (cooperative); 64 threads per action.
+template <int AM, int NJ>
+__global__ __launch_bounds__(AM * kWave) void k_fib_coop(DevModel m, FibCells fc,
+                                                         const float *staytab, float *al0,
+                                                         float *al1, float *out, SweepCtl c) {
+  __shared__ FibShared<AM> sh;
+  __shared__ double red[2 * kMaxWaves];
+  __shared__ int s_stop;
+  const int a = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const FibMoves<NJ> mv(SlipLanes(m), a);
+  fib_tables<AM>(m, staytab, sh);
+  const bool rvec = m.A == AM && (reinterpret_cast<uintptr_t>(m.R) & 15u) == 0;
+  FibRows<AM> f;
+  fib_cells_load<AM>(fc, blockIdx.x, f);
+  __syncthreads();
+  const int kend = coop_sweeps(c, al0, al1, red, &s_stop,
+                               [&](const float *in, float *o, double &r, double &vm) {
+    fib_rows_load<AM, true>(m, a, in, false, rvec, f);
+    fib_pass<AM, NJ, true>(m, fc, mv, sh, a, in, o, false, rvec, f, r, vm);
+  });
+  if (kend) coop_result(c, kend, al0, al1, out, (long long)m.S * m.A);
+}
+
+// Per-sweep form of sweep k (nothing once the rule has fired).
+template <int AM, int NJ>
+__global__ __launch_bounds__(AM * kWave, NJ == 4 ? 4 : 2) void k_fib_sweep(DevModel m, FibCells fc,
+                                                          const float *staytab, const float *ain,
+                                                          float *aout, int k, SweepCtl c) {
+  __shared__ FibShared<AM> sh;
+  __shared__ double red[2 * kMaxWaves];
+  const int a = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const bool vec = m.A == AM, rvec = vec && (reinterpret_cast<uintptr_t>(m.R) & 15u) == 0;
+  FibRows<AM> f;
+  fib_cells_load<AM>(fc, blockIdx.x, f);
+  fib_tables<AM>(m, staytab, sh);
+  const FibMoves<NJ> mv(SlipLanes(m), a);
+  fib_rows_load<AM, false>(m, a, ain, vec, rvec, f);   // (in flight during the check)
+  if (sweep_stopped(c, k, red)) return;
   double r = 0.0, vm = 0.0;
-  fib_pass<AM, false, OP>(m, sig, staytab, ain, aout, ctab, (long long)gridDim.x * kBlock, r,
-                          vm);
-  sweep_report(r, vm, c.res, c.vmax, k, red);
+  fib_pass<AM, NJ, false>(m, fc, mv, sh, a, ain, aout, vec, rvec, f, r, vm);
+  sweep_part_store(c, k, r, vm, red);
+}
+
+// The blind bound, in the same two forms.
+template <int AM>
+__global__ __launch_bounds__(kBlock) void k_blind_coop(DevModel m, const uint32_t *sig,
+                                                       const float *staytab, float *al0,
+                                                       float *al1, float *out, SweepCtl c) {
+  __shared__ double red[2 * kMaxWaves];
+  __shared__ int s_stop;
+  const SlipLanes sl(m);
+  const int kend = coop_sweeps(c, al0, al1, red, &s_stop,
+                               [&](const float *in, float *o, double &r, double &vm) {
+    blind_pass<AM, true>(m, sl, sig, staytab, in, o, (long long)gridDim.x * kBlock, r, vm);
+  });
+  if (kend) coop_result(c, kend, al0, al1, out, (long long)m.S * m.A);
+}
+
+template <int AM>
+__global__ __launch_bounds__(kBlock) void k_blind_sweep(DevModel m, const uint32_t *sig,
+                                                        const float *staytab, const float *ain,
+                                                        float *aout, int k, SweepCtl c) {
+  __shared__ double red[2 * kMaxWaves];
+  const SlipLanes sl(m);
+  if (sweep_stopped(c, k, red)) return;
+  double r = 0.0, vm = 0.0;
+  blind_pass<AM, false>(m, sl, sig, staytab, ain, aout, (long long)gridDim.x * kBlock, r, vm);
+  sweep_part_store(c, k, r, vm, red);
 }
 
 // ---------------------------------------------------------------------------
@@ -620,11 +1039,10 @@ __global__ __launch_bounds__(kBlock) void k_fib_sweep(DevModel m, const uint32_t
 // Workspace: sig [S], staytab [A][256], two value buffers of `vals` floats,
 // res and vmax [max_sweeps + 2], then barrier counter, residual and sweep
 // count, error word.
-static size_t sweep_ws(const qv_model *m, long long vals, int max_sweeps) {
-  const size_t S = (size_t)m->W * m->H;
+static size_t sweep_ws(long long S, int A, long long vals, int max_sweeps) {
   size_t off = 0;
-  off += align_up(S * 4, 256);
-  off += align_up((size_t)m->A * 256 * 4, 256);
+  off += align_up((size_t)S * 4, 256);
+  off += align_up((size_t)A * 256 * 4, 256);
   off += 2 * align_up((size_t)vals * 4, 256);
   off += 2 * align_up((size_t)(max_sweeps + 2) * 8, 256);
   off += 256;   // barrier counter, residual, sweep count
@@ -634,11 +1052,33 @@ static size_t sweep_ws(const qv_model *m, long long vals, int max_sweeps) {
 }
 
 size_t vi_ws(const qv_model *m, int max_sweeps) {
-  return sweep_ws(m, (long long)m->W * m->H, max_sweeps);
+  const long long S = (long long)m->W * m->H;
+  return sweep_ws(S, m->A, S, max_sweeps);
+}
+
+// The FIB solve's sorted cells lie behind the sweep workspace.
+static int fib_blocks(long long S) { return (int)((S + kBlock - 1) / kBlock); }
+static FibCells fib_cells(char *p, long long S, size_t *bytes) {
+  FibCells f;
+  size_t off = 0;
+  f.cells = (int32_t *)(p + off);
+  off += align_up((size_t)S * 4, 256);
+  f.recs = (uint64_t *)(p + off);
+  off += align_up((size_t)S * 8, 256);
+  f.counts = (int32_t *)(p + off);
+  off += align_up((size_t)kFibClasses * fib_blocks(S) * 4, 256);
+  f.ctl = (int32_t *)(p + off);
+  off += 256;
+  f.nfree = 0;
+  if (bytes) *bytes = off;
+  return f;
 }
 
 size_t fib_ws(const qv_model *m, int max_sweeps) {
-  return sweep_ws(m, (long long)m->W * m->H * m->A, max_sweeps);
+  const long long S = (long long)m->W * m->H;
+  size_t bytes;
+  fib_cells(nullptr, S, &bytes);
+  return sweep_ws(S, m->A, S * m->A, max_sweeps) + bytes;
 }
 
 struct SweepWs {
@@ -677,35 +1117,39 @@ static SweepWs carve(const DevModel &m, long long vals, int max_sweeps, float to
   return w;
 }
 
-// Map signature, stay table, cleared records and x_0 = 0.
+// Map signature, stay table, cleared records and both value buffers 0 (x_0,
+// and the blocked cells' values, which a FIB sweep does not write).
 static hipError_t sweep_setup(const DevModel &m, const SweepWs &w, long long vals,
                               hipStream_t st) {
   hipError_t e = launch_prep(m, w.sig, w.staytab, w.err, st);
   if (e != hipSuccess) return e;
   const long long n = std::max<long long>(w.c.max_sweeps + 2, vals);
   QV_LAUNCH(k_sweep_fill, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, w.c.res,
-            w.c.vmax, w.c.max_sweeps + 2, w.c.bar, w.x[0], vals);
+            w.c.vmax, w.c.max_sweeps + 2, w.c.bar, w.x[0], w.x[1], vals);
   return hipGetLastError();
 }
 
 // Grids up to this many cells take the one-launch form; larger ones the
 // per-sweep launches.  Measured on MI355X (a sweep, one-launch vs
-// per-sweep): 4096 cells, value iteration 12.3 vs 15.3 us, FIB 44.7 vs 46.4;
-// 262144 cells, value iteration 20.4 vs 16.4, FIB 138 vs 123, blind bound
-// 162 vs 46 -- at that size the coherent loads of the gathered values (past
+// per-sweep): 4096 cells, value iteration 12.3 vs 15.3 us; 262144 cells, value
+// iteration 20.4 vs 16.4, blind bound 162 vs 46 -- at that size the coherent loads of the gathered values (past
 // the L2) cost more than the launches they save.
 constexpr long long kCoopMaxCells = 16384;
+// FIB, by cells times actions, a solve, one launch / per sweep: 64x64x8 1.11 /
+// 1.31 ms, 100x40x9 2.50 / 3.24, 512x30x8 3.28 / 2.83, 128x128x8 2.62 / 2.38.
+constexpr long long kFibCoopMaxValues = 65536;
 
 // Workgroups of a cooperative launch of `kernel`: at most `want`, and no
 // more than can be resident at once; 0 for the per-sweep form: a grid of
 // more than kCoopMaxCells cells, no cooperative launch on this device, or
 // QVTS_SWEEP_LAUNCHES=1.  QVTS_SWEEP_COOP=1 takes the one-launch form at
 // any size.
-static int coop_grid(const void *kernel, size_t lds, int want, long long cells) {
+static int coop_grid(const void *kernel, int threads, size_t lds, int want, long long size,
+                     long long most) {
   const char *e = std::getenv("QVTS_SWEEP_LAUNCHES");
   if (e && std::atoi(e) == 1) return 0;
   const char *f = std::getenv("QVTS_SWEEP_COOP");
-  if (!(f && std::atoi(f) == 1) && cells > kCoopMaxCells) return 0;
+  if (!(f && std::atoi(f) == 1) && size > most) return 0;
   int dev = 0, coop = 0, cus = 0, per = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 0;
   if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess ||
@@ -713,10 +1157,20 @@ static int coop_grid(const void *kernel, size_t lds, int want, long long cells) 
     return 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, kBlock, lds) != hipSuccess ||
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, threads, lds) != hipSuccess ||
       per < 1)
     return 0;
   return std::max(1, std::min(std::min(want, per * cus), kMaxCoopGrid));
+}
+
+// Workgroups of `kernel` that are resident at once on the device.
+static int resident_grid(const void *kernel, int threads, size_t lds) {
+  int dev = 0, cus = 0, per = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, threads, lds) != hipSuccess)
+    return kSweepGrid;
+  return std::max(1, per * cus);
 }
 
 // Residual and sweep count of a cooperative solve (one wait); a barrier
@@ -735,11 +1189,11 @@ static hipError_t read_result(const SweepWs &w, double *residual, int *sweeps,
   return aborted ? hipErrorLaunchTimeOut : hipSuccess;
 }
 
-// Per-sweep form: `launch(k, in, out)` enqueues sweep k; every kViChunk
-// sweeps the host reads the chunk's residuals and stops at the first sweep
+// Per-sweep form: `launch(k, in, out)` enqueues sweep k on g workgroups; every
+// kViChunk sweeps the host reads the chunk's residuals and stops at the first sweep
 // that meets the rule.  Returns the last sweep in *sweeps.
 template <class F>
-static hipError_t sweep_chunks(const SweepWs &w, F launch, double *residual, int *sweeps,
+static hipError_t sweep_chunks(const SweepWs &w, int g, F launch, double *residual, int *sweeps,
                                hipStream_t st) {
   std::vector<unsigned long long> hres(kViChunk), hvm(kViChunk);
   const int max_sweeps = w.c.max_sweeps;
@@ -748,6 +1202,7 @@ static hipError_t sweep_chunks(const SweepWs &w, F launch, double *residual, int
   for (int k0 = 1; k0 <= max_sweeps && !done; k0 += kViChunk) {
     const int k1 = std::min(max_sweeps, k0 + kViChunk - 1);
     for (int k = k0; k <= k1; ++k) launch(k, w.x[(k - 1) & 1], w.x[k & 1]);
+    QV_LAUNCH(k_sweep_close, dim3(1), dim3(kBlock), 0, st, w.c, k1, g);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int cnt = k1 - k0 + 1;
@@ -780,7 +1235,8 @@ hipError_t run_value_iteration(const DevModel &m, float tol, int max_sweeps, flo
   const int TH = tile_rows(m.W, m.H);
   const int tiles = (m.H + TH - 1) / TH;
   const size_t lds = (size_t)(TH + 2) * (m.W + 2) * sizeof(float);
-  const int G = coop_grid(reinterpret_cast<const void *>(&k_vi_coop), lds, tiles, m.S);
+  const int G = coop_grid(reinterpret_cast<const void *>(&k_vi_coop), kBlock, lds, tiles, m.S,
+                          kCoopMaxCells);
   if (G > 0) {
     DevModel mm = m;
     const uint32_t *sig = w.sig;
@@ -797,10 +1253,11 @@ hipError_t run_value_iteration(const DevModel &m, float tol, int max_sweeps, flo
     if (e != hipSuccess) return e;
     return read_result(w, residual, sweeps, st);
   }
+  const int g = std::min(tiles, kSweepGrid);
   e = sweep_chunks(
-      w,
+      w, g,
       [&](int k, float *in, float *out) {
-        QV_LAUNCH(k_vi_sweep, dim3(tiles), dim3(kBlock), lds, st, m, w.sig, w.staytab, TH, in,
+        QV_LAUNCH(k_vi_sweep, dim3(g), dim3(kBlock), lds, st, m, w.sig, w.staytab, TH, tiles, in,
                   out, k, w.c);
       },
       residual, sweeps, st);
@@ -813,39 +1270,106 @@ hipError_t run_value_iteration(const DevModel &m, float tol, int max_sweeps, flo
   return hipStreamSynchronize(st);
 }
 
-template <int AM, int OP>
-static hipError_t run_fib_am(const DevModel &m, const SweepWs &w, float *alpha,
-                             double *residual, int *sweeps, hipStream_t st) {
-  const long long vals = (long long)m.S * m.A;
-  const int want = (int)std::min<long long>((m.S + kBlock - 1) / kBlock, 1 << 20);
-  const int G = coop_grid(reinterpret_cast<const void *>(&k_fib_coop<AM, OP>), 0, want, m.S);
+template <class F>
+static hipError_t coop_solve(const SweepWs &w, const char *name, const void *kernel, int G,
+                             int threads, F args_of, double *residual, int *sweeps,
+                             hipStream_t st) {
   hipError_t e;
+  {
+    TimingScope ts(name, st);
+    e = args_of([&](void **args) {
+      return hipLaunchCooperativeKernel(kernel, dim3(G), dim3(threads), args, 0u, st);
+    });
+  }
+  if (e != hipSuccess) return e;
+  return read_result(w, residual, sweeps, st);
+}
+
+// alpha after a per-sweep solve.
+static hipError_t sweep_copy(const SweepWs &w, float *alpha, long long vals, int sweeps,
+                             hipStream_t st) {
+  const hipError_t e =
+      hipMemcpyAsync(alpha, w.x[sweeps & 1], (size_t)vals * 4, hipMemcpyDeviceToDevice, st);
+  return e != hipSuccess ? e : hipStreamSynchronize(st);
+}
+
+template <int AM, int NJ>
+static hipError_t run_fib_am(const DevModel &m, const SweepWs &w, FibCells fc, float *alpha,
+                             double *residual, int *sweeps, hipStream_t st) {
+  const int nb = fib_blocks(m.S);
+  QV_LAUNCH(k_fib_count, dim3(nb), dim3(kBlock), 0, st, m, w.sig, fc.counts);
+  QV_LAUNCH(k_fib_scan, dim3(1), dim3(1024), 0, st, fc.counts, kFibClasses * nb, fc.ctl);
+  QV_LAUNCH(k_fib_scatter, dim3(nb), dim3(kBlock), 0, st, m, w.sig, fc.counts, fc.cells, fc.recs);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  // the count as a launch argument: a sweep then starts with its cells
+  e = hipMemcpyAsync(&fc.nfree, fc.ctl, 4, hipMemcpyDeviceToHost, st);
+  if (e != hipSuccess) return e;
+  e = hipStreamSynchronize(st);
+  if (e != hipSuccess) return e;
+  const int threads = m.A * kWave;
+  const int want = std::max(1, (fc.nfree + kWave - 1) / kWave);
+  const void *coop = reinterpret_cast<const void *>(&k_fib_coop<AM, NJ>);
+  const int G = coop_grid(coop, threads, 0, want, (long long)m.S * m.A, kFibCoopMaxValues);
+  if (G > 0) {
+    DevModel mm = m;
+    const float *stay = w.staytab;
+    float *a0 = w.x[0], *a1 = w.x[1];
+    SweepCtl c = w.c;
+    return coop_solve(
+        w, "k_fib_coop", coop, G, threads,
+        [&](auto launch) {
+          void *args[] = {&mm, &fc, &stay, &a0, &a1, &alpha, &c};
+          return launch(args);
+        },
+        residual, sweeps, st);
+  }
+  // as many workgroups as are resident at once: they take the groups in turn,
+  // and a part-filled second round would cost as much as the first (512x512,
+  // a sweep: 1024 workgroups 34.9 us, 768 32.2, the resident 512 25.7)
+  const int g = std::min(want, std::min(kSweepGrid, resident_grid(
+      reinterpret_cast<const void *>(&k_fib_sweep<AM, NJ>), threads, 0)));
+  e = sweep_chunks(
+      w, g,
+      [&](int k, float *in, float *out) {
+        QV_LAUNCH((k_fib_sweep<AM, NJ>), dim3(g), dim3(threads), 0, st, m, fc, w.staytab, in, out,
+                  k, w.c);
+      },
+      residual, sweeps, st);
+  if (e != hipSuccess) return e;
+  return sweep_copy(w, alpha, (long long)m.S * m.A, *sweeps, st);
+}
+
+template <int AM>
+static hipError_t run_blind_am(const DevModel &m, const SweepWs &w, float *alpha,
+                               double *residual, int *sweeps, hipStream_t st) {
+  const int want = fib_blocks(m.S);
+  const void *coop = reinterpret_cast<const void *>(&k_blind_coop<AM>);
+  const int G = coop_grid(coop, kBlock, 0, want, m.S, kCoopMaxCells);
   if (G > 0) {
     DevModel mm = m;
     const uint32_t *sig = w.sig;
     const float *stay = w.staytab;
     float *a0 = w.x[0], *a1 = w.x[1];
     SweepCtl c = w.c;
-    void *args[] = {&mm, &sig, &stay, &a0, &a1, &alpha, &c};
-    {
-      TimingScope ts(OP == 0 ? "k_fib_coop" : "k_blind_coop", st);
-      e = hipLaunchCooperativeKernel(reinterpret_cast<const void *>(&k_fib_coop<AM, OP>),
-                                     dim3(G), dim3(kBlock), args, 0u, st);
-    }
-    if (e != hipSuccess) return e;
-    return read_result(w, residual, sweeps, st);
+    return coop_solve(
+        w, "k_blind_coop", coop, G, kBlock,
+        [&](auto launch) {
+          void *args[] = {&mm, &sig, &stay, &a0, &a1, &alpha, &c};
+          return launch(args);
+        },
+        residual, sweeps, st);
   }
-  e = sweep_chunks(
-      w,
+  const int g = std::min(want, kSweepGrid);
+  const hipError_t e = sweep_chunks(
+      w, g,
       [&](int k, float *in, float *out) {
-        QV_LAUNCH((k_fib_sweep<AM, OP>), dim3(want), dim3(kBlock), 0, st, m, w.sig, w.staytab,
-                  in, out, k, w.c);
+        QV_LAUNCH((k_blind_sweep<AM>), dim3(g), dim3(kBlock), 0, st, m, w.sig, w.staytab, in, out,
+                  k, w.c);
       },
       residual, sweeps, st);
   if (e != hipSuccess) return e;
-  e = hipMemcpyAsync(alpha, w.x[*sweeps & 1], (size_t)vals * 4, hipMemcpyDeviceToDevice, st);
-  if (e != hipSuccess) return e;
-  return hipStreamSynchronize(st);
+  return sweep_copy(w, alpha, (long long)m.S * m.A, *sweeps, st);
 }
 
 // op 0: the FIB equation; op 1: the blind-policy equation.
@@ -853,16 +1377,32 @@ hipError_t run_fib(const DevModel &m, float tol, int max_sweeps, float *alpha,
                    double *residual, int *sweeps, char *ws, hipStream_t st, int op) {
   const long long vals = (long long)m.S * m.A;
   const SweepWs w = carve(m, vals, max_sweeps, tol, ws);
+  const FibCells fc = fib_cells(ws + sweep_ws(m.S, m.A, vals, max_sweeps), m.S, nullptr);
   hipError_t e = sweep_setup(m, w, vals, st);
   if (e != hipSuccess) return e;
   if (op == 1) {
-    if (m.A <= 4) return run_fib_am<4, 1>(m, w, alpha, residual, sweeps, st);
-    if (m.A <= 8) return run_fib_am<8, 1>(m, w, alpha, residual, sweeps, st);
-    return run_fib_am<9, 1>(m, w, alpha, residual, sweeps, st);
+    if (m.A <= 4) return run_blind_am<4>(m, w, alpha, residual, sweeps, st);
+    if (m.A <= 8) return run_blind_am<8>(m, w, alpha, residual, sweeps, st);
+    return run_blind_am<9>(m, w, alpha, residual, sweeps, st);
   }
-  if (m.A <= 4) return run_fib_am<4, 0>(m, w, alpha, residual, sweeps, st);
-  if (m.A <= 8) return run_fib_am<8, 0>(m, w, alpha, residual, sweeps, st);
-  return run_fib_am<9, 0>(m, w, alpha, residual, sweeps, st);
+  // the rows a wavefront holds: its own cell's and one per move with a
+  // probability (four at most in the usual slip tables: 3 moves and, of nine
+  // actions, none that needs more)
+  int most = 0;
+  for (int a = 0; a < m.A; ++a) {
+    int n = 0;
+    for (int k = 0; k < 9; ++k) n += k != 4 && m.slip[a * 9 + k] != 0.f;
+    most = std::max(most, n);
+  }
+  const bool few = most <= 4;
+  if (m.A <= 4)
+    return few ? run_fib_am<4, 4>(m, w, fc, alpha, residual, sweeps, st)
+               : run_fib_am<4, 8>(m, w, fc, alpha, residual, sweeps, st);
+  if (m.A <= 8)
+    return few ? run_fib_am<8, 4>(m, w, fc, alpha, residual, sweeps, st)
+               : run_fib_am<8, 8>(m, w, fc, alpha, residual, sweeps, st);
+  return few ? run_fib_am<9, 4>(m, w, fc, alpha, residual, sweeps, st)
+             : run_fib_am<9, 8>(m, w, fc, alpha, residual, sweeps, st);
 }
 
 }  // namespace qv
