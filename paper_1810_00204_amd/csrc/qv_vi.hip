@@ -6,18 +6,20 @@
 //       alpha^a(x) = R(x,a) + gamma sum_z max_a' sum_x' O(z|x') T(x,a,x') alpha^a'(x').
 // Both are Jacobi sweeps in FP32.  The residual of sweep k, max |x_k - x_{k-1}|
 // over free cells (and actions), is formed in FP64 (exact for a difference
-// of two FP32 values) and max-reduced with an integer atomic on its bit
-// pattern, which is order independent.
+// of two FP32 values); workgroups leave their maxima in slots, and a maximum
+// does not depend on their order.
 //
-// On small and medium grids all sweeps of a solve run in one cooperative
-// launch: every workgroup is resident, and after each sweep the workgroups
-// meet at a grid barrier, read the sweep's residual and max |value| and so
-// all stop after the same sweep (the stopping rule sees the same numbers
-// everywhere); the host waits once, at the end.  On large grids (and where a
-// cooperative launch is not possible) the sweeps are launched one by one,
-// each doing nothing once the rule has fired, and the host reads the
-// residuals every kViChunk sweeps.  Both forms do the same arithmetic per
-// cell, so their results are bitwise equal.
+// Value iteration needs little arithmetic per cell and sweep, so its launches
+// do several sweeps each: a workgroup holds a region of the grid, of which the
+// inner part stays exact for as many sweeps as the rim is wide.  A grid that
+// one workgroup holds is solved in one launch.  FIB and the blind bound do one
+// sweep per launch, or, on small grids, all sweeps in one cooperative launch:
+// every workgroup is resident, and after each sweep the workgroups meet at a
+// grid barrier, read the sweep's residual and max |value| and so all stop
+// after the same sweep (the stopping rule sees the same numbers everywhere).
+// Launches after the one in which the rule fired do nothing, and the host
+// looks at the residuals every few launches.  All forms do the same arithmetic
+// per cell, so their results are bitwise equal.
 #include <algorithm>
 #include <cstdlib>
 #include <cstring>
@@ -27,7 +29,7 @@
 
 namespace qv {
 
-constexpr int kViChunk = 32;
+constexpr int kViChunk = 64;   // sweeps between two looks at the residuals
 constexpr int kMaxCoopGrid = 4096;   // workgroups of a one-launch solve at most
 // workgroups of a sweep launch at most: four per CU; more would only add
 // residual slots for every workgroup to read
@@ -96,6 +98,7 @@ struct SweepCtl {
   double *out_res;                  // residual of the last sweep
   int *out_k;                       // number of sweeps run
   unsigned int *abort;              // set when a barrier wait gave up
+  unsigned int *arrive, *stop;      // value iteration: workgroups done, whether the rule fired
   double *part;                     // [2][2][grid]: per-workgroup r, max |x| of a sweep
   int max_sweeps;
   double tol;
@@ -245,6 +248,7 @@ __global__ void k_sweep_fill(unsigned long long *res, unsigned long long *vmax, 
   if (i == 0) {
     bar[0] = 0ull;   // barrier counter
     bar[2] = 0ull;   // sweep count and abort flag
+    bar[3] = 0ull;   // arrivals and stop flag
   }
   if (i < nx) {
     x0[i] = 0.f;
@@ -256,181 +260,271 @@ __global__ void k_sweep_fill(unsigned long long *res, unsigned long long *vmax, 
 // Q-MDP value iteration
 // ---------------------------------------------------------------------------
 
-// V band: off-grid and blocked cells read as zero (their value is 0), the
-// goal keeps its value.
-template <bool COH>
-__device__ __forceinline__ void load_vband(const DevModel &m, const uint32_t *sig,
-                                           const float *V, int y0, int th, float *band,
-                                           int BW) {
-  constexpr int kBatch = 8;   // band entries whose loads a thread issues together
-  const int n = (th + 2) * BW;
-  const float rBW = 1.0f / (float)BW;
-  for (int i0 = threadIdx.x; i0 < n; i0 += kBatch * kBlock) {
-    int cell[kBatch];
-    uint32_t sg[kBatch];
-    float v[kBatch];
-    // every lane loads (cell 0 for halo and padding lanes) and masks after,
-    // so the batch's loads go out together
+// The slip table in a register per lane: lane 3 a + k % 3 of register k / 3
+// holds T'(a,k), so that an entry is one lane read and not a scalar load that
+// the next instruction waits for.
+struct SlipLanes {
+  float v[3];
+  uint64_t nz[3];   // lanes that are not 0
+  __device__ __forceinline__ explicit SlipLanes(const DevModel &m) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const bool has = lane < 3 * m.A;
 #pragma unroll
-    for (int j = 0; j < kBatch; ++j) {
-      const int i = i0 + j * kBlock;
-      const int r = fdiv(i, BW, rBW);
-      const int gy = y0 - 1 + r, gx = i - r * BW - 1;
-      const bool in = i < n && gy >= 0 && gy < m.H && gx >= 0 && gx < m.W;
-      cell[j] = in ? gy * m.W + gx : -1;
-      sg[j] = sig[in ? cell[j] : 0];
-      v[j] = ld_val<COH>(V + (in ? cell[j] : 0));
+    for (int i = 0; i < 3; ++i) {
+      v[i] = has ? m.slip[lane / 3 * 9 + 3 * i + lane % 3] : 0.f;
+      nz[i] = __ballot(v[i] != 0.f);
     }
+  }
+  __device__ __forceinline__ bool moves(int a, int k) const {
+    return (nz[k / 3] >> (3 * a + k % 3)) & 1ull;
+  }
+  __device__ __forceinline__ float at(int a, int k) const {
+    return __int_as_float(
+        __builtin_amdgcn_readlane(__float_as_int(v[k / 3]), 3 * a + k % 3));
+  }
+};
+
+// Row t of an alpha or reward table into registers.
+template <int AM, bool COH>
+__device__ __forceinline__ void value_row(const float *al, int t, int A, bool vec, float (&v)[AM]) {
+  if constexpr (!COH && AM % 4 == 0) {
+    if (vec) {   // rows of AM values, 16-byte aligned
+      const float4 *q = reinterpret_cast<const float4 *>(al + (size_t)t * AM);
 #pragma unroll
-    for (int j = 0; j < kBatch; ++j) {
-      const int i = i0 + j * kBlock;
-      if (i < n) band[i] = (cell[j] >= 0 && (sg[j] & kSigFree)) ? v[j] : 0.f;
+      for (int i = 0; i < AM / 4; ++i) {
+        const float4 f = q[i];
+        v[4 * i] = f.x;
+        v[4 * i + 1] = f.y;
+        v[4 * i + 2] = f.z;
+        v[4 * i + 3] = f.w;
+      }
+      return;
     }
   }
+  // (columns beyond A repeat column 0)
+#pragma unroll
+  for (int ap = 0; ap < AM; ++ap) v[ap] = ld_val<COH>(al + (size_t)t * A + (ap < A ? ap : 0));
 }
 
-// Q(s,a) = R(s,a) + gamma * (sum_k T'(a,k) V(s + d_k) + stay(s,a) V(s)):
-// the expectation over T(s,a,.) of Sec. V, with the band zero where a move
-// fails (its mass is in `stay`).
-__device__ __forceinline__ float q_backup(const DevModel &m, const float *c, int BW,
-                                          const float *sl, float stay, float r) {
-  float v = sl[0] * c[-BW - 1];
-  v = fmaf(sl[1], c[-BW], v);
-  v = fmaf(sl[2], c[-BW + 1], v);
-  v = fmaf(sl[3], c[-1], v);
-  v = fmaf(sl[5], c[1], v);
-  v = fmaf(sl[6], c[BW - 1], v);
-  v = fmaf(sl[7], c[BW], v);
-  v = fmaf(sl[8], c[BW + 1], v);
-  v = fmaf(stay, c[0], v);
-  return fmaf(m.gamma, v, r);
+// A workgroup's region: kViX columns by kViY rows, a thread per column and
+// strip of kViStrip rows.  With a rim of kViRim cells on each side the inner
+// kViOutX x kViOutY cells are exact after kViRim sweeps (what lies beyond the
+// region reads as 0, and the error moves in by one cell a sweep).  Why these
+// sizes: 512x512 makes 256 regions, one per CU; the rim costs 2.2 times the
+// cells and saves seven of eight launches, each longer than a sweep's work.
+// A thread's cells, their map bits and reward rows and the slip table stay in
+// registers for all sweeps of a launch (two wavefronts per SIMD leave room for
+// 256).  Bound by the vector ALU and, between sweeps, the barrier.  Measured,
+// 512x512, 218 sweeps: one launch per sweep 3.6 ms, this 1.2 ms; skipping the
+// moves of probability 0 by a scalar branch each, 1.5 ms.
+constexpr int kViX = 48, kViStrip = 5, kViGroups = 10, kViY = kViStrip * kViGroups;
+constexpr int kViRim = 8, kViOutX = kViX - 2 * kViRim, kViOutY = kViY - 2 * kViRim;
+constexpr int kViBlock = 512, kViPitch = kViX + 2;
+static_assert(kViX * kViGroups <= kViBlock, "a thread per column and strip");
+
+// Work of a launch.  Block: `ns` sweeps k0 + 1 .. k0 + ns from V_{k0} into
+// Vout, unless the rule fired before.  Table: `ns` sweeps, then Q of the next
+// one.  Solve: sweeps until the rule fires, then Q of the last.
+enum ViMode { kViBlockMode, kViTableMode, kViSolveMode };
+
+template <int AM>
+struct ViShared {
+  float v[2][(kViY + 2) * kViPitch];
+  float stay[AM * 256];
+  double red[kViRim][2][kViBlock / kWave];
+  int last;
+};
+
+// Q(s,a) = R(s,a) + gamma * (sum_k T'(a,k) V(s + d_k) + stay(s,a) V(s)) for
+// the strip's cells, the expectation over T(s,a,.) of Sec. V: V reads as 0
+// where a move fails (its mass is in `stay`).  w: the strip's 3-column window.
+template <int AM>
+__device__ __forceinline__ void vi_strip_q(const DevModel &m, const float (&T)[AM][9],
+                                           const float *stay, const uint32_t (&info)[kViStrip],
+                                           const float (&w)[kViStrip + 2][3],
+                                           const float (&R)[kViStrip][AM], int a,
+                                           float (&q)[kViStrip]) {
+#pragma unroll
+  for (int r = 0; r < kViStrip; ++r) q[r] = 0.f;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    if (k == 4) continue;
+    const float t = T[a][k];
+#pragma unroll
+    for (int r = 0; r < kViStrip; ++r) q[r] = fmaf(t, w[r + k / 3][k % 3], q[r]);
+  }
+#pragma unroll
+  for (int r = 0; r < kViStrip; ++r) {
+    q[r] = fmaf(stay[a * 256 + (int)sig_out8(info[r])], w[r + 1][1], q[r]);
+    q[r] = fmaf(m.gamma, (info[r] & kSigGoal) ? w[r + 1][1] : q[r], R[r][a]);
+  }
 }
 
-__device__ __forceinline__ float cell_q(const DevModel &m, const float *band, int BW, int ly,
-                                        int lx, uint32_t sg, const float *staytab, int a,
-                                        int t) {
-  const float *c = band + (ly + 1) * BW + lx + 1;
-  const float r = m.R[(size_t)t * m.A + a];
-  if (sg & kSigGoal) return fmaf(m.gamma, c[0], r);
-  return q_backup(m, c, BW, &m.slip[a * 9], staytab[a * 256 + sig_out8(sg)], r);
-}
-
-// One band of sweep k: V_k from V_{k-1} (in the LDS band); the band's
-// largest |V_k - V_{k-1}| and |V_k| (free cells) are folded into r, vm.
-template <bool COH>
-__device__ __forceinline__ void vi_band(const DevModel &m, const uint32_t *sig,
-                                        const float *staytab, int TH, int tile,
-                                        const float *Vin, float *Vout, float *band, double &r,
-                                        double &vm) {
-  const int W = m.W, BW = W + 2;
-  const int y0 = tile * TH;
-  const int th = min(TH, m.H - y0);
-  load_vband<COH>(m, sig, Vin, y0, th, band, BW);
-  __syncthreads();
-  const float rW = 1.0f / (float)W;
-  for (int i = threadIdx.x; i < th * W; i += kBlock) {
-    const int ly = fdiv(i, W, rW), lx = i - ly * W;
-    const int t = (y0 + ly) * W + lx;
-    const uint32_t sg = sig[t];
-    float best = 0.f;
-    if (sg & kSigFree) {
-      best = -INFINITY;
-      for (int a = 0; a < m.A; ++a)
-        best = fmaxf(best, cell_q(m, band, BW, ly, lx, sg, staytab, a, t));
-      const double d = fabs((double)best - (double)band[(ly + 1) * BW + lx + 1]);
-      r = fmax(r, d);
-      vm = fmax(vm, fabs((double)best));
+template <int AM, ViMode MODE>
+__global__ __launch_bounds__(kViBlock) void k_vi(DevModel m, const uint32_t *sig,
+                                                 const float *staytab, int regions_x,
+                                                 const float *Vin, float *Vout, float *Q, int k0,
+                                                 int ns, double *slots, SweepCtl c) {
+  __shared__ ViShared<AM> sh;
+  const int A = m.A, W = m.W, H = m.H, tid = threadIdx.x;
+  const int lane = tid & (kWave - 1), wave = tid / kWave;
+  const int col = tid % kViX, strip = tid / kViX;
+  const bool act = strip < kViGroups;
+  const int ry = blockIdx.x / regions_x, rx = blockIdx.x - ry * regions_x;
+  const int rim = MODE == kViSolveMode ? 0 : kViRim;
+  const int x = rx * kViOutX - rim + col, y0 = ry * kViOutY - rim + strip * kViStrip;
+  // ---- the strip's cells
+  uint32_t info[kViStrip];
+  float R[kViStrip][AM];
+  bool own[kViStrip];
+  const bool rvec = A == AM && AM % 4 == 0 && (reinterpret_cast<uintptr_t>(m.R) & 15u) == 0;
+  const bool stopped = MODE == kViBlockMode && *c.stop;
+#pragma unroll
+  for (int r = 0; r < kViStrip; ++r) {
+    const int y = y0 + r, ly = strip * kViStrip + r;
+    const bool in = act && x >= 0 && x < W && y >= 0 && y < H;
+    const int t = in ? y * W + x : 0;
+    info[r] = in ? sig[t] : 0u;
+    own[r] = in && (MODE == kViSolveMode ||
+                    (col >= kViRim && col < kViRim + kViOutX && ly >= kViRim &&
+                     ly < kViRim + kViOutY));
+    value_row<AM, false>(m.R, t, A, rvec, R[r]);
+    const float v = in && MODE != kViSolveMode ? Vin[t] : 0.f;
+    if (act) sh.v[0][(ly + 1) * kViPitch + col + 1] = (info[r] & kSigFree) ? v : 0.f;
+  }
+  for (int i = tid; i < A * 256; i += kViBlock) sh.stay[i] = staytab[i];
+  // the entries around the region, in both buffers
+  for (int i = tid; i < 2 * (kViX + kViY + 2); i += kViBlock) {
+    const int e = i < 2 * kViPitch ? (i < kViPitch ? i : (kViY + 1) * kViPitch + i - kViPitch)
+                                   : (1 + (i - 2 * kViPitch) / 2) * kViPitch +
+                                         ((i & 1) ? kViPitch - 1 : 0);
+    sh.v[0][e] = sh.v[1][e] = 0.f;
+  }
+  const SlipLanes sl(m);
+  if (stopped) return;   // (the same in every thread)
+  float T[AM][9];   // the slip table (kept there: as scalars it does not fit)
+#pragma unroll
+  for (int a = 0; a < AM; ++a)
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+      if (k == 4) continue;
+      T[a][k] = sl.at(a < A ? a : 0, k);
+      asm volatile("" : "+v"(T[a][k]));
     }
-    st_val<COH>(Vout + t, best);
-  }
-  __syncthreads();   // the band is reused by the next tile
-}
-
-// Q(t, .) of one band from V (the Q-values of a sweep from its input V).
-template <bool COH>
-__device__ __forceinline__ void vi_q_band(const DevModel &m, const uint32_t *sig,
-                                          const float *staytab, int TH, int tile, const float *V,
-                                          float *Q, float *band) {
-  const int W = m.W, BW = W + 2;
-  const int y0 = tile * TH;
-  const int th = min(TH, m.H - y0);
-  load_vband<COH>(m, sig, V, y0, th, band, BW);
   __syncthreads();
-  const float rW = 1.0f / (float)W;
-  for (int i = threadIdx.x; i < th * W; i += kBlock) {
-    const int ly = fdiv(i, W, rW), lx = i - ly * W;
-    const int t = (y0 + ly) * W + lx;
-    const uint32_t sg = sig[t];
-    for (int a = 0; a < m.A; ++a)
-      Q[(size_t)t * m.A + a] =
-          (sg & kSigFree) ? cell_q(m, band, BW, ly, lx, sg, staytab, a, t) : 0.f;
-  }
-  __syncthreads();
-}
-
-// Every sweep in one launch (cooperative: all workgroups resident).  V[0]
-// holds V_0 = 0; sweep k writes V_k into V[k & 1].  After the last sweep kc
-// the workgroups write Q_kc (from V_{kc-1}) into Q.
-__global__ __launch_bounds__(kBlock) void k_vi_coop(DevModel m, const uint32_t *sig,
-                                                    const float *staytab, int TH, int tiles,
-                                                    float *V0, float *V1, float *Q,
-                                                    SweepCtl c) {
-  extern __shared__ float smem[];
-  __shared__ double red[2 * kMaxWaves];
-  __shared__ int s_stop;
-  if (threadIdx.x == 0) s_stop = 0;
-  int kend = c.max_sweeps;
-  for (int k = 1; k <= c.max_sweeps; ++k) {
-    const float *Vin = (k & 1) ? V0 : V1;
-    float *Vout = (k & 1) ? V1 : V0;
-    double r = 0.0, vm = 0.0;
-    for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x)
-      vi_band<true>(m, sig, staytab, TH, tile, Vin, Vout, smem, r, vm);
-    sweep_part_store(c, k, r, vm, red);
-    grid_sync(c.bar, (unsigned long long)k * gridDim.x, c.abort);
-    if (threadIdx.x < kWave) {
-      const int conv = sweep_part_decide(c, k);
-      if (threadIdx.x == 0)
-        s_stop = __hip_atomic_load(c.abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? 2
-                                                                                        : conv;
+  const float *stay = sh.stay;
+  const int pos = strip * kViStrip * kViPitch + col;
+  auto window = [&](const float *v, float (&w)[kViStrip + 2][3]) {
+#pragma unroll
+    for (int r = 0; r < kViStrip + 2; ++r)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) w[r][j] = v[pos + r * kViPitch + j];
+  };
+  int kend = 0;
+  for (int k = 1; k <= ns; ++k) {
+    const float *vi = sh.v[(k - 1) & 1];
+    float *vo = sh.v[k & 1];
+    double res = 0.0, vm = 0.0;
+    if (act) {
+      float w[kViStrip + 2][3], best[kViStrip], q[kViStrip];
+      window(vi, w);
+#pragma unroll
+      for (int r = 0; r < kViStrip; ++r) best[r] = -INFINITY;
+#pragma unroll
+      for (int a = 0; a < AM; ++a) {
+        if (a >= A) continue;
+        vi_strip_q<AM>(m, T, stay, info, w, R, a, q);
+#pragma unroll
+        for (int r = 0; r < kViStrip; ++r) best[r] = fmaxf(best[r], q[r]);
+      }
+#pragma unroll
+      for (int r = 0; r < kViStrip; ++r) {
+        const bool fr = (info[r] & kSigFree) != 0u;
+        vo[pos + (r + 1) * kViPitch + 1] = fr ? best[r] : 0.f;
+        if (fr && own[r]) {
+          res = fmax(res, fabs((double)best[r] - (double)w[r + 1][1]));
+          vm = fmax(vm, fabs((double)best[r]));
+        }
+      }
+    }
+    if constexpr (MODE != kViTableMode) {
+      res = wave_max(res);
+      vm = wave_max(vm);
+      if (lane == 0) {
+        sh.red[(k - 1) % kViRim][0][wave] = res;
+        sh.red[(k - 1) % kViRim][1][wave] = vm;
+      }
     }
     __syncthreads();
-    if (s_stop) {   // the same decision in every workgroup (unless aborted)
+    if constexpr (MODE == kViSolveMode) {
+      res = vm = 0.0;
+#pragma unroll
+      for (int i = 0; i < kViBlock / kWave; ++i) {
+        res = fmax(res, sh.red[(k - 1) % kViRim][0][i]);
+        vm = fmax(vm, sh.red[(k - 1) % kViRim][1][i]);
+      }
       kend = k;
-      break;
+      if (tid == 0) *c.out_res = res;
+      if (res == 0.0 || res <= c.tol * fmax(1.0, vm)) break;
     }
   }
-  if (s_stop == 2) return;
-  const float *Vprev = (kend & 1) ? V0 : V1;
-  for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x)
-    vi_q_band<true>(m, sig, staytab, TH, tile, Vprev, Q, smem);
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    *c.out_k = kend;
-    *c.out_res = load_bits(c.res + kend);
+  if constexpr (MODE == kViBlockMode) {
+    const float *v = sh.v[ns & 1];
+#pragma unroll
+    for (int r = 0; r < kViStrip; ++r)
+      if (own[r]) Vout[(y0 + r) * W + x] = v[pos + (r + 1) * kViPitch + 1];
+    // the region's maxima, by sweep; the last workgroup to leave them folds
+    // all regions' and sets the stop flag if the rule fired in this block
+    const int G = gridDim.x;
+    if (tid < 2 * ns) {
+      const int j = tid >> 1;
+      double f = 0.0;
+      for (int i = 0; i < kViBlock / kWave; ++i) f = fmax(f, sh.red[j][tid & 1][i]);
+      __hip_atomic_store(slots + (size_t)tid * G + blockIdx.x, f, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (tid == 0)
+      sh.last = __hip_atomic_fetch_add(c.arrive, 1u, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT) == (unsigned)G - 1u;
+    __syncthreads();
+    if (!sh.last) return;
+    for (int j = wave; j < ns; j += kViBlock / kWave) {
+      double res = 0.0, vm = 0.0;
+      for (int g = lane; g < G; g += kWave) {
+        res = fmax(res, __hip_atomic_load(slots + (size_t)(2 * j) * G + g, __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_AGENT));
+        vm = fmax(vm, __hip_atomic_load(slots + (size_t)(2 * j + 1) * G + g, __ATOMIC_RELAXED,
+                                        __HIP_MEMORY_SCOPE_AGENT));
+      }
+      res = wave_max(res);
+      vm = wave_max(vm);
+      if (lane == 0) {
+        c.res[k0 + 1 + j] = (unsigned long long)__double_as_longlong(res);
+        c.vmax[k0 + 1 + j] = (unsigned long long)__double_as_longlong(vm);
+        if (res == 0.0 || res <= c.tol * fmax(1.0, vm)) *c.stop = 1u;
+      }
+    }
+    if (tid == 0) *c.arrive = 0u;
+    return;
   }
-}
-
-// Per-sweep form: sweep k >= 1, V_k from V_{k-1}; does nothing once the
-// rule has fired at an earlier sweep.
-__global__ __launch_bounds__(kBlock) void k_vi_sweep(DevModel m, const uint32_t *sig,
-                                                     const float *staytab, int TH, int tiles,
-                                                     const float *Vin, float *Vout, int k,
-                                                     SweepCtl c) {
-  extern __shared__ float smem[];
-  __shared__ double red[2 * kMaxWaves];
-  if (sweep_stopped(c, k, red)) return;
-  double r = 0.0, vm = 0.0;
-  for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x)
-    vi_band<false>(m, sig, staytab, TH, tile, Vin, Vout, smem, r, vm);
-  sweep_part_store(c, k, r, vm, red);
-}
-
-// Q_k(s,.) from V_{k-1}, the Q-values of the last sweep (same arithmetic).
-__global__ __launch_bounds__(kBlock) void k_vi_q(DevModel m, const uint32_t *sig,
-                                                 const float *staytab, int TH, const float *V,
-                                                 float *Q) {
-  extern __shared__ float smem[];
-  vi_q_band<false>(m, sig, staytab, TH, blockIdx.x, V, Q, smem);
+  // Q from the values in buffer `at`: in a solve those before the last sweep
+  const int at = MODE == kViSolveMode ? (kend - 1) & 1 : ns & 1;
+  if (act) {
+    float w[kViStrip + 2][3], q[kViStrip];
+    window(sh.v[at], w);
+#pragma unroll
+    for (int a = 0; a < AM; ++a) {
+      if (a >= A) continue;
+      vi_strip_q<AM>(m, T, stay, info, w, R, a, q);
+#pragma unroll
+      for (int r = 0; r < kViStrip; ++r)
+        if (own[r])
+          Q[((size_t)(y0 + r) * W + x) * A + a] = (info[r] & kSigFree) ? q[r] : 0.f;
+    }
+  }
+  if (MODE == kViSolveMode && tid == 0) *c.out_k = kend;
 }
 
 // ---------------------------------------------------------------------------
@@ -533,30 +627,6 @@ __global__ __launch_bounds__(kBlock) void k_fib_scatter(DevModel m, const uint32
   recs[at] = rec;
 }
 
-// The slip table in a register per lane: lane 3 a + k % 3 of register k / 3
-// holds T'(a,k), so that an entry is one lane read and not a scalar load that
-// the next instruction waits for.
-struct SlipLanes {
-  float v[3];
-  uint64_t nz[3];   // lanes that are not 0
-  __device__ __forceinline__ explicit SlipLanes(const DevModel &m) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const bool has = lane < 3 * m.A;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      v[i] = has ? m.slip[lane / 3 * 9 + 3 * i + lane % 3] : 0.f;
-      nz[i] = __ballot(v[i] != 0.f);
-    }
-  }
-  __device__ __forceinline__ bool moves(int a, int k) const {
-    return (nz[k / 3] >> (3 * a + k % 3)) & 1ull;
-  }
-  __device__ __forceinline__ float at(int a, int k) const {
-    return __int_as_float(
-        __builtin_amdgcn_readlane(__float_as_int(v[k / 3]), 3 * a + k % 3));
-  }
-};
-
 // The FIB right-hand side.  The successors of a free cell x are its neighbours
 // k != 4 that a move enters and x itself, which takes the stay mass:
 // T(x,a,x + d_k) = T'(a,k), T(x,a,x) = stay(x,a).  With C[zw][w] the
@@ -591,28 +661,6 @@ struct FibShared {
   float ctab[256];
   int cell[kWave];
 };
-
-// Row t of an alpha or reward table into registers.
-template <int AM, bool COH>
-__device__ __forceinline__ void fib_row(const float *al, int t, int A, bool vec, float (&v)[AM]) {
-  if constexpr (!COH && AM % 4 == 0) {
-    if (vec) {   // rows of AM values, 16-byte aligned
-      const float4 *q = reinterpret_cast<const float4 *>(al + (size_t)t * AM);
-#pragma unroll
-      for (int i = 0; i < AM / 4; ++i) {
-        const float4 f = q[i];
-        v[4 * i] = f.x;
-        v[4 * i + 1] = f.y;
-        v[4 * i + 2] = f.z;
-        v[4 * i + 3] = f.w;
-      }
-      return;
-    }
-  }
-  // (columns beyond A repeat column 0)
-#pragma unroll
-  for (int ap = 0; ap < AM; ++ap) v[ap] = ld_val<COH>(al + (size_t)t * A + (ap < A ? ap : 0));
-}
 
 template <int AM>
 __device__ __forceinline__ float fib_row_max(const float (&v)[AM]) {
@@ -732,10 +780,10 @@ __device__ __forceinline__ void fib_rows_load(const DevModel &m, int a, const fl
     const int k = a + i * A;
     if (k > 9) continue;
     if (k == 9) {
-      fib_row<AM, false>(m.R, f.x, A, rvec, f.v[i]);
+      value_row<AM, false>(m.R, f.x, A, rvec, f.v[i]);
     } else {
       const bool ok = k == 4 || ((out8 >> (k < 4 ? k : k - 1)) & 1u);
-      fib_row<AM, COH>(ain, ok ? f.x + (k / 3 - 1) * W + (k % 3 - 1) : f.x, A, vec, f.v[i]);
+      value_row<AM, COH>(ain, ok ? f.x + (k / 3 - 1) * W + (k % 3 - 1) : f.x, A, vec, f.v[i]);
     }
   }
 }
@@ -1051,9 +1099,17 @@ static size_t sweep_ws(long long S, int A, long long vals, int max_sweeps) {
   return off;
 }
 
+// Regions of a value iteration, and its residual slots behind the sweep
+// workspace.
+static int vi_regions_x(int W) { return (W + kViOutX - 1) / kViOutX; }
+static int vi_regions(int W, int H) {
+  return vi_regions_x(W) * ((H + kViOutY - 1) / kViOutY);
+}
+
 size_t vi_ws(const qv_model *m, int max_sweeps) {
   const long long S = (long long)m->W * m->H;
-  return sweep_ws(S, m->A, S, max_sweeps);
+  return sweep_ws(S, m->A, S, max_sweeps) +
+         align_up((size_t)2 * kViRim * vi_regions(m->W, m->H) * 8, 256);
 }
 
 // The FIB solve's sorted cells lie behind the sweep workspace.
@@ -1108,6 +1164,8 @@ static SweepWs carve(const DevModel &m, long long vals, int max_sweeps, float to
   w.c.out_res = (double *)(ws + off + 8);
   w.c.out_k = (int *)(ws + off + 16);
   w.c.abort = (unsigned int *)(ws + off + 20);
+  w.c.arrive = (unsigned int *)(ws + off + 24);
+  w.c.stop = (unsigned int *)(ws + off + 28);
   off += 256;
   w.err = (int32_t *)(ws + off);
   off += 256;
@@ -1227,47 +1285,66 @@ static hipError_t sweep_chunks(const SweepWs &w, int g, F launch, double *residu
   return hipSuccess;
 }
 
+template <int AM>
+static hipError_t run_vi_am(const DevModel &m, const SweepWs &w, double *slots, float *Q,
+                            double *residual, int *sweeps, hipStream_t st) {
+  const int max_sweeps = w.c.max_sweeps;
+  // the environment's switch to single sweeps, as in the other solves
+  const char *e1 = std::getenv("QVTS_SWEEP_LAUNCHES");
+  const bool single = e1 && std::atoi(e1) == 1;
+  if (!single && m.W <= kViX && m.H <= kViY) {
+    QV_LAUNCH((k_vi<AM, kViSolveMode>), dim3(1), dim3(kViBlock), 0, st, m, w.sig, w.staytab, 1,
+              w.x[0], w.x[1], Q, 0, max_sweeps, slots, w.c);
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : read_result(w, residual, sweeps, st);
+  }
+  const int rx = vi_regions_x(m.W), G = vi_regions(m.W, m.H), step = single ? 1 : kViRim;
+  std::vector<unsigned long long> hres(kViChunk), hvm(kViChunk);
+  hipError_t e;
+  bool done = false;
+  int kc = 0;
+  for (int k0 = 0; k0 < max_sweeps && !done; k0 += kViChunk) {
+    const int k1 = std::min(max_sweeps, k0 + kViChunk);
+    for (int k = k0; k < k1; k += step)   // block b reads x[b & 1] and writes the other
+      QV_LAUNCH((k_vi<AM, kViBlockMode>), dim3(G), dim3(kViBlock), 0, st, m, w.sig, w.staytab, rx,
+                w.x[(k / step) & 1], w.x[(k / step + 1) & 1], Q, k, std::min(step, k1 - k), slots,
+                w.c);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const int cnt = k1 - k0;
+    e = hipMemcpyAsync(hres.data(), w.c.res + k0 + 1, cnt * 8, hipMemcpyDeviceToHost, st);
+    if (e != hipSuccess) return e;
+    e = hipMemcpyAsync(hvm.data(), w.c.vmax + k0 + 1, cnt * 8, hipMemcpyDeviceToHost, st);
+    if (e != hipSuccess) return e;
+    e = hipStreamSynchronize(st);
+    if (e != hipSuccess) return e;
+    for (int i = 0; i < cnt && !done; ++i) {
+      double r, vm;
+      memcpy(&r, &hres[i], 8);
+      memcpy(&vm, &hvm[i], 8);
+      *residual = r;
+      kc = k0 + i + 1;
+      done = r == 0.0 || r <= w.c.tol * std::max(1.0, vm);
+    }
+  }
+  *sweeps = kc;
+  // Q of sweep kc, from the start of its block
+  const int b = (kc - 1) / step;
+  QV_LAUNCH((k_vi<AM, kViTableMode>), dim3(G), dim3(kViBlock), 0, st, m, w.sig, w.staytab, rx,
+            w.x[b & 1], w.x[(b + 1) & 1], Q, b * step, kc - 1 - b * step, slots, w.c);
+  e = hipGetLastError();
+  return e != hipSuccess ? e : hipStreamSynchronize(st);
+}
+
 hipError_t run_value_iteration(const DevModel &m, float tol, int max_sweeps, float *Q,
                                double *residual, int *sweeps, char *ws, hipStream_t st) {
   const SweepWs w = carve(m, m.S, max_sweeps, tol, ws);
-  hipError_t e = sweep_setup(m, w, m.S, st);
+  const hipError_t e = sweep_setup(m, w, m.S, st);
   if (e != hipSuccess) return e;
-  const int TH = tile_rows(m.W, m.H);
-  const int tiles = (m.H + TH - 1) / TH;
-  const size_t lds = (size_t)(TH + 2) * (m.W + 2) * sizeof(float);
-  const int G = coop_grid(reinterpret_cast<const void *>(&k_vi_coop), kBlock, lds, tiles, m.S,
-                          kCoopMaxCells);
-  if (G > 0) {
-    DevModel mm = m;
-    const uint32_t *sig = w.sig;
-    const float *stay = w.staytab;
-    int th = TH, nt = tiles;
-    float *v0 = w.x[0], *v1 = w.x[1];
-    SweepCtl c = w.c;
-    void *args[] = {&mm, &sig, &stay, &th, &nt, &v0, &v1, &Q, &c};
-    {
-      TimingScope ts("k_vi_coop", st);
-      e = hipLaunchCooperativeKernel(reinterpret_cast<const void *>(&k_vi_coop), dim3(G),
-                                     dim3(kBlock), args, (unsigned)lds, st);
-    }
-    if (e != hipSuccess) return e;
-    return read_result(w, residual, sweeps, st);
-  }
-  const int g = std::min(tiles, kSweepGrid);
-  e = sweep_chunks(
-      w, g,
-      [&](int k, float *in, float *out) {
-        QV_LAUNCH(k_vi_sweep, dim3(g), dim3(kBlock), lds, st, m, w.sig, w.staytab, TH, tiles, in,
-                  out, k, w.c);
-      },
-      residual, sweeps, st);
-  if (e != hipSuccess) return e;
-  const int kc = *sweeps;
-  QV_LAUNCH(k_vi_q, dim3(tiles), dim3(kBlock), lds, st, m, w.sig, w.staytab, TH,
-            w.x[(kc - 1) & 1], Q);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return hipStreamSynchronize(st);
+  double *slots = (double *)(ws + sweep_ws(m.S, m.A, m.S, max_sweeps));
+  if (m.A <= 4) return run_vi_am<4>(m, w, slots, Q, residual, sweeps, st);
+  if (m.A <= 8) return run_vi_am<8>(m, w, slots, Q, residual, sweeps, st);
+  return run_vi_am<9>(m, w, slots, Q, residual, sweeps, st);
 }
 
 template <class F>
