@@ -376,6 +376,8 @@ __device__ __forceinline__ float filter_scale(float U) {
 
 // Workgroup barrier for LDS alone: stores to global memory stay in flight
 // (__syncthreads waits for them; each thread reads back only its own).
+// Also where an LDS write of the loop's end meets a barrier at its top: there
+// the compiler has left the wait of __syncthreads out.
 __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
@@ -549,7 +551,7 @@ __global__ __launch_bounds__(kFMaxBlock) void k_filter(DevModel m, FilterArgs fa
     auto az_at = [&](int i) {
       if (i / kFChunk != azc) {
         azc = i / kFChunk;
-        __syncthreads();
+        lds_barrier();   // (its wait is its own: see lds_barrier)
         for (int j = tid; j < kFChunk; j += NT) {
           const int g = azc * kFChunk + j;
           sh.az[j] = g < fa.T ? at[g] + 256 * zt[g] : 0;
@@ -561,7 +563,7 @@ __global__ __launch_bounds__(kFMaxBlock) void k_filter(DevModel m, FilterArgs fa
     auto u_at = [&](int i) {
       if (i / kFChunk != uc) {
         uc = i / kFChunk;
-        __syncthreads();
+        lds_barrier();
         for (int j = tid; j < kFChunk; j += NT) sh.u[j] = usum[min(uc * kFChunk + j, fa.T - 1)];
         __syncthreads();
       }
