@@ -36,6 +36,7 @@ struct qv_batch {
   std::vector<qv_model> models;
   std::vector<int> D;
   int tile_cells = 0, chunk = 1;
+  bool pp = true;               // phases 0, 1 by (parent, band) items over all actions
   // layout of the current shape
   std::vector<PlanLayout> lay;
   std::vector<size_t> qoff;
@@ -98,6 +99,13 @@ bool layout(qv_batch *b, int tile_cells, bool commit) {
   long long pb = 0, lb = 0, sb = 0;
   size_t lds0 = 0, lds1 = 0, lds2 = 0;
   int apad1 = 4, apad2 = 4;
+  // (parent, band) items over all actions where every band fits a thread's
+  // kParentCells; wider bands take one item per action
+  bool pp = true;
+  for (int q = 0; q < nq; ++q) {
+    const qv_model &m = b->models[q];
+    if ((long long)band_rows(m.W, m.H, tile_cells) * m.W > kParentCells * kBlock) pp = false;
+  }
   for (int q = 0; q < nq; ++q) {
     const qv_model &m = b->models[q];
     const int th = band_rows(m.W, m.H, tile_cells);
@@ -105,7 +113,8 @@ bool layout(qv_batch *b, int tile_cells, bool commit) {
     qoff[q] = take(lay[q].pub.total_bytes);
     const qv_tree_layout &T = lay[q].pub;
     // the last level of a query with A <= 8 runs (parent, leaf band) items in
-    // phase 2; every other level runs (parent, band, action) items in phases 0, 1
+    // phase 2; every other level runs (parent, band) items (a last level of 9
+    // actions: (parent, band, action) items) in phases 0, 1
     const bool lp = m.A <= 8;
     for (int d = 0; d < b->dmax; ++d) {
       for (int ph = 0; ph < 3; ++ph) {
@@ -113,7 +122,7 @@ bool layout(qv_batch *b, int tile_cells, bool commit) {
         long long items = 0;
         const bool banded = d + 1 < b->D[q] || (d + 1 == b->D[q] && !lp);
         if (ph < 2 && banded)
-          items = T.level_slots[d] * T.tiles * m.A;
+          items = T.level_slots[d] * T.tiles * (pp && d + 1 < b->D[q] ? 1 : m.A);
         else if (ph == 2 && d + 1 == b->D[q] && lp)
           items = T.level_slots[d] * lay[q].leaf_tiles;
         tot[ph * b->dmax + d] += items;
@@ -131,6 +140,7 @@ bool layout(qv_batch *b, int tile_cells, bool commit) {
     lb += (m.L + 255) / 256;
     if (pb > (1LL << 30)) return false;
     lds0 = std::max(lds0, band_lds_bytes(m.W, th) + (size_t)16 * kBlock * 4);
+    if (pp) lds0 = std::max(lds0, stats_parent_lds_bytes(m.W, th, m.L));
     if (lp) {
       const int am = m.A <= 4 ? 4 : 8;
       apad2 = std::max(apad2, am);
@@ -180,6 +190,7 @@ bool layout(qv_batch *b, int tile_cells, bool commit) {
   b->apad[1] = apad1;
   b->apad[2] = apad2;
   b->tile_cells = tile_cells;
+  b->pp = pp;
   b->bound_ws = nullptr;
   drop_graphs(b);
   return true;
@@ -193,7 +204,7 @@ bool size_grids(qv_batch *b) {
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return false;
   for (int ph = 0; ph < 3; ++ph) {
-    const int occ = batch_level_occupancy(ph, b->apad[ph], b->lds[ph]);
+    const int occ = batch_level_occupancy(ph, b->apad[ph], b->lds[ph], b->pp);
     if (occ <= 0) return false;
     for (int d = 0; d < b->dmax; ++d) {
       const long long visits =
@@ -347,7 +358,7 @@ hipError_t enqueue_level(const qv_batch *b, char *ws, int d, hipStream_t st, boo
   }
   for (int ph = 0; ph < 3; ++ph) {
     e = launch_batch_level(level_args(b, ws, d, ph), ph, b->apad[ph], b->lds[ph],
-                           b->grid[ph][d], st, timed);
+                           b->grid[ph][d], b->pp, st, timed);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

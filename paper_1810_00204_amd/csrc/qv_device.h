@@ -10,6 +10,7 @@ namespace qv {
 
 constexpr int kBlock = 256;   // threads per workgroup for the tiled kernels
 constexpr int kWave = 64;     // CDNA wavefront width
+constexpr int kParentCells = 8;   // cells per thread of a per-parent band: at most 2048 / kBlock
 // ints per sorted leaf band: kBlock chunk ranges, the first chunk of each
 // wall reading (17), the first sorted position of each wall reading (17)
 constexpr int kSortChunkInts = 2 * kBlock + 34;

@@ -208,9 +208,11 @@ size_t leaf_lds_bytes(int W, int TH, int K, int A);
 hipError_t launch_batch_prep(const BatchPrep &bp, int cell_blocks, int lm_blocks,
                              int sort_blocks, hipStream_t st, bool timed);
 size_t leaf_parent_lds_bytes(int W, int TH, int L, int AM);
+size_t stats_parent_lds_bytes(int W, int TH, int L);
+// pp: phases 0 and 1 by (parent, band) items over all actions
 hipError_t launch_batch_level(const BatchLevel &bl, int phase, int apad, size_t lds, int grid,
-                              hipStream_t st, bool timed);
-int batch_level_occupancy(int phase, int apad, size_t lds);
+                              bool pp, hipStream_t st, bool timed);
+int batch_level_occupancy(int phase, int apad, size_t lds, bool pp);
 hipError_t launch_batch_out(int nq, const int32_t *act_in, const float *rq_in, int32_t *act_out,
                             float *rq_out, hipStream_t st);
 

@@ -589,6 +589,23 @@ __device__ __forceinline__ float range_sum(const float *x, int stride, int lo, i
   return ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
 }
 
+// A batch's descriptors do not change while a kernel runs: read through the
+// constant address space they come by scalar loads (through an ordinary
+// pointer every lane loads every word, again after each store).  The pointers
+// in them are to global memory, which the compiler cannot see: left generic,
+// every access through them is a flat one, which waits for LDS as well.
+// (By way of an integer: a cast straight there and back is dropped.)
+#define QV_CONST_AS __attribute__((address_space(4)))
+#define QV_GLOBAL_AS __attribute__((address_space(1)))
+template <typename T>
+__device__ __forceinline__ const T &const_ref(const T *p) {
+  return *(const T *)(const QV_CONST_AS T *)(uintptr_t)p;
+}
+template <typename T>
+__device__ __forceinline__ T *as_global(T *p) {
+  return (T *)(QV_GLOBAL_AS T *)(uintptr_t)p;
+}
+
 // Hand-off between workgroups of one launch.  Values another workgroup will
 // read are written with device-scope atomic stores (written through to the
 // device-coherent level, past this XCD's L2), the writer waits until its
@@ -1023,7 +1040,7 @@ __device__ void stats_item(const DevModel &m, const LevelArgs &lv, Item it, floa
   const float *stay_a = s_stay;
   const float rho = m.lm_p;
   const int L = m.L;
-  const float *Rt = m.R;
+  const float *Rt = as_global(m.R);
   float h0 = 0.f, racc = 0.f;
   const int t00 = y0 * W;
   for (int i0 = tid; i0 < ncell; i0 += kCellBatch * kBlock) {
@@ -1183,8 +1200,6 @@ __global__ __launch_bounds__(kBlock) void k_update(DevModel m, LevelArgs lv) {
 // that each load the band.  The per-action arithmetic is that of stats_item
 // and update_item, in the same order, so results are bitwise the same.
 // ---------------------------------------------------------------------------
-constexpr int kParentCells = 8;   // cells per thread of a band: at most 2048 / kBlock
-
 struct ParentShared {
   float stay[QV_MAX_ACTIONS * 256];   // stay probability by neighbour pattern, per action
   float red[QV_MAX_ACTIONS][kBlock / kWave];
@@ -1254,7 +1269,7 @@ __device__ void stats_parent_item(const DevModel &m, const LevelArgs &lv, int p,
   for (int j = 0; j < kParentCells; ++j) {
     if (j >= jn) break;
     const int i = tid + j * kBlock;
-    const float *row = m.R + (size_t)(t00 + (i < ncell ? i : 0)) * A;
+    const float *row = as_global(m.R) + (size_t)(t00 + (i < ncell ? i : 0)) * A;
     float rv[QV_MAX_ACTIONS];
 #pragma unroll
     for (int a = 0; a < QV_MAX_ACTIONS; ++a) rv[a] = row[a < A ? a : 0];
@@ -2197,7 +2212,7 @@ __device__ void leaf_parent_item(const DevModel &m, const LevelArgs &lv, const T
 #pragma unroll
   for (int a = 0; a < AM; ++a) racc[a] = 0.f;
   if (lv.own_reward) {
-    const float *Rt = m.R;
+    const float *Rt = as_global(m.R);
     const bool r_vec = (A == AM) && ((reinterpret_cast<uintptr_t>(Rt) & 15u) == 0);
     const int ncell = th * W, t00 = y0 * W;
     for (int i0 = tid; i0 < ncell; i0 += 4 * NT) {
@@ -3099,48 +3114,60 @@ hipError_t launch_plan(const qv_model *mm, const float *Q, const float *b0, int 
 // that spans every query of the batch
 // ---------------------------------------------------------------------------
 
-// Query owning item i: the last q with base[q] <= i (base[nq] = total).
+// Query owning item i: the last q with base[q] <= i (base[nq] = total).  The
+// lanes compare 512 entries at a time, so the search waits for memory once (a
+// binary search waits once per halving, eight times for 256 queries).
 __device__ __forceinline__ int find_query(const int32_t *base, int nq, int i) {
-  int lo = 0, hi = nq;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (base[mid] <= i)
-      lo = mid;
-    else
-      hi = mid;
-  }
-  return lo;
-}
-
-// A copy of a descriptor read from device memory, declared uniform word by
-// word so that it lives in scalar registers (the compiler cannot prove the
-// memory unchanged under the kernel's own stores, so it would load it per lane).
-template <typename T>
-__device__ __forceinline__ T uniform_copy(const T &src) {
-  static_assert(sizeof(T) % 4 == 0, "word-sized descriptor");
-  T out;
-  const int *in = reinterpret_cast<const int *>(&src);
-  int *o = reinterpret_cast<int *>(&out);
+  const int lane = threadIdx.x & (kWave - 1);
+  int n = 0;   // entries <= i; they come first
+  for (int k0 = 0; k0 < nq; k0 += 8 * kWave) {
+    int v[8];
 #pragma unroll
-  for (int i = 0; i < (int)(sizeof(T) / 4); ++i) o[i] = __builtin_amdgcn_readfirstlane(in[i]);
-  return out;
+    for (int j = 0; j < 8; ++j) v[j] = base[min(k0 + j * kWave + lane, nq)];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      n += __popcll(__ballot(k0 + j * kWave + lane < nq && v[j] <= i));
+    if (n < k0 + 8 * kWave) break;
+  }
+  return n - 1;
 }
 
 __device__ __forceinline__ LevelArgs bind_level(const BatchQuery &bq, const BatchCall &c, int d) {
-  LevelArgs lv = uniform_copy(bq.lv[d]);
-  const BatchCall cu = uniform_copy(c);
-  lv.Q = cu.Q;
-  lv.q_vec = cu.q_vec;
-  lv.key0 = cu.key0;
-  lv.key1 = cu.key1;
-  lv.qid = cu.qid;
-  if (d == 0) lv.pbel = cu.b0;
+  LevelArgs lv = bq.lv[d];
+  lv.Q = c.Q;
+  lv.q_vec = c.q_vec;
+  lv.key0 = c.key0;
+  lv.key1 = c.key1;
+  lv.qid = c.qid;
+  if (d == 0) lv.pbel = c.b0;
+  lv.pbel = as_global(lv.pbel);
+  lv.pvalid = as_global(lv.pvalid);
+  lv.part = as_global(lv.part);
+  lv.lmv = as_global(lv.lmv);
+  lv.cvalid = as_global(lv.cvalid);
+  lv.cz = as_global(lv.cz);
+  lv.ccount = as_global(lv.ccount);
+  lv.cpz = as_global(lv.cpz);
+  lv.reward = as_global(lv.reward);
+  lv.cbel = as_global(lv.cbel);
+  lv.leafpart = as_global(lv.leafpart);
+  lv.Q = as_global(lv.Q);
+  lv.sig = as_global(lv.sig);
+  lv.staytab = as_global(lv.staytab);
+  lv.lm_wall = as_global(lv.lm_wall);
+  lv.ctr = as_global(lv.ctr);
+  lv.creward = as_global(lv.creward);
+  lv.sort_cells = as_global(lv.sort_cells);
+  lv.sort_chunk = as_global(lv.sort_chunk);
+  lv.slot_list = as_global(lv.slot_list);
+  lv.slot_n = as_global(lv.slot_n);
+  lv.porder = as_global(lv.porder);
   return lv;
 }
 
 __global__ void k_prep_batch(BatchPrep bp) {
-  const int q = find_query(bp.base, bp.nq, blockIdx.x);
-  const BatchQuery &bq = bp.q[q];
+  const int q = __builtin_amdgcn_readfirstlane(find_query(bp.base, bp.nq, blockIdx.x));
+  const BatchQuery &bq = const_ref(bp.q + q);
   const long long g = (long long)(blockIdx.x - bp.base[q]) * blockDim.x + threadIdx.x;
   prep_sig_one(bq.m, bq.sig, bq.staytab, bq.err, bq.px, g);
   if (g < QV_MAX_ACTIONS) bq.tr.rootQ_out[g] = 0.f;   // entries a >= A stay 0
@@ -3149,8 +3176,8 @@ __global__ void k_prep_batch(BatchPrep bp) {
 
 // leaf-band sort of the queries whose last level runs k_leaf_parent items
 __global__ __launch_bounds__(kBlock) void k_prep_sort_batch(BatchPrep bp) {
-  const int q = find_query(bp.sort_base, bp.nq, blockIdx.x);
-  const BatchQuery &bq = bp.q[q];
+  const int q = __builtin_amdgcn_readfirstlane(find_query(bp.sort_base, bp.nq, blockIdx.x));
+  const BatchQuery &bq = const_ref(bp.q + q);
   const LevelArgs &lv = bq.lv[bq.D - 1];
   const int band = blockIdx.x - bp.sort_base[q];
   const int TC = lv.TH * bq.m.W, c_lo = band * TC;
@@ -3159,52 +3186,84 @@ __global__ __launch_bounds__(kBlock) void k_prep_sort_batch(BatchPrep bp) {
 }
 
 __global__ void k_prep_landmarks_batch(BatchPrep bp) {
-  const int q = find_query(bp.lm_base, bp.nq, blockIdx.x);
-  const BatchQuery &bq = bp.q[q];
+  const int q = __builtin_amdgcn_readfirstlane(find_query(bp.lm_base, bp.nq, blockIdx.x));
+  const BatchQuery &bq = const_ref(bp.q + q);
   const int l = (blockIdx.x - bp.lm_base[q]) * blockDim.x + threadIdx.x;
   prep_landmark_one(bq.m, bq.sig, bq.err, bq.px.lm_wall, l);
 }
 
-// PHASE 0: statistics and draws of the Q-nodes of level d (k_stats);
-// PHASE 1: child beliefs (k_update) or, at the last level of a query with
-// 9 actions, leaf scoring and backup (k_leaf);
+// PHASE 0: statistics and draws of the Q-nodes of level d (k_stats_parent, or
+// k_stats for bands above kParentCells per thread);
+// PHASE 1: child beliefs (k_update_parent, k_update) or, at the last level of
+// a query with 9 actions, leaf scoring and backup (k_leaf);
 // PHASE 2: the last level of a query with at most 8 actions, per (parent,
-// band) over all actions (k_leaf_parent).  Workgroups take `chunk` items at a time from the
-// queue until it runs dry; every workgroup leaves after one failed take.
+// band) over all actions (k_leaf_parent).
+// An item of phases 0 and 1 is a (parent, band) with all its actions (PP; a
+// last level with 9 actions and PP = false: one action), so a band is loaded
+// once; results are bitwise those of an item per action.  Workgroups take
+// `chunk` items at a time from the queue until it runs dry; every workgroup
+// leaves after one failed take.
+// An item is a few microseconds of work, so what it waits for ahead of its
+// band counts as much: the next take is in flight while the current items are
+// worked on, the search for the item's query waits for memory once, the
+// descriptors come by scalar loads, and nothing goes through generic pointers.
+// Statistics at four workgroups a CU (4 registers spilled) 1.1 ms, at two
+// (189 registers) 1.4.  Measured, 256 queries of sides 32..256 (phases 0, 1,
+// 2): 2.5, 2.6, 3.2 -> 1.0, 0.7, 2.9 ms; the batch 7.92 -> 4.35 ms.
 // (phase 2 runs k_leaf_parent's 512-thread form, so a query's results equal
 // those of its single-query plan bit for bit)
-template <int PHASE, int APAD>
-__global__ __launch_bounds__(PHASE == 2 ? kLeafBlock : kBlock, PHASE == 2 && APAD == 4 ? 4 : 1) void k_level_batch(BatchLevel bl) {
+template <int PHASE, int APAD, bool PP>
+__global__ __launch_bounds__(PHASE == 2 ? kLeafBlock : kBlock, PHASE == 2 && APAD == 4 ? 4 : PHASE == 0 && PP ? 4 : 1) void k_level_batch(BatchLevel bl) {
   extern __shared__ float smem[];
   __shared__ BandShared sh;
+  __shared__ ParentShared shp;       // per-parent items only
   __shared__ LeafParentShared shl;   // phase 2 only
   __shared__ int s_item;
+  if (threadIdx.x == 0) s_item = atomicAdd(bl.queue, bl.chunk);
   for (;;) {
-    __syncthreads();
-    if (threadIdx.x == 0) s_item = atomicAdd(bl.queue, bl.chunk);
     __syncthreads();
     const int i0 = s_item;
     if (i0 >= bl.total) break;
+    int next = 0;
+    if (threadIdx.x == 0) {
+      // (an address that the compiler does not know to be uniform: else it
+      // makes one add for the wavefront and waits for it here)
+      int z = 0;
+      asm volatile("" : "+v"(z));
+      next = atomicAdd(bl.queue + z, bl.chunk);
+    }
     const int i1 = min(i0 + bl.chunk, bl.total);
     for (int i = i0; i < i1; ++i) {
       const int q = __builtin_amdgcn_readfirstlane(find_query(bl.base, bl.nq, i));
-      const BatchQuery &bq = bl.q[q];
-      const LevelArgs lv = bind_level(bq, bl.call[q], bl.d);
-      const Item it = decode_item(i - bl.base[q], lv.tiles, bq.m.A);
-      if constexpr (PHASE == 0) {
-        stats_item(bq.m, lv, it, smem, sh);
-      } else if constexpr (PHASE == 1) {
-        if (bl.d + 1 < bq.D)
+      const BatchQuery &bq = const_ref(bl.q + q);
+      const LevelArgs lv = bind_level(bq, const_ref(bl.call + q), bl.d);
+      const int local = __builtin_amdgcn_readfirstlane(i - bl.base[q]);
+      const bool leaf = bl.d + 1 == bq.D;
+      if constexpr (PHASE == 2) {
+        leaf_parent_item<APAD, -1, kLeafBlock>(bq.m, lv, bq.tr, local / lv.tiles, local % lv.tiles,
+                                               smem, shl);
+      } else if (PP && !leaf) {
+        const int p = local / lv.tiles, tile = local - p * lv.tiles;
+        if constexpr (PHASE == 0)
+          stats_parent_item(bq.m, lv, p, tile, smem, shp);
+        else
+          update_parent_item(bq.m, lv, p, tile, 0, bq.m.A, smem, shp);
+      } else {
+        const Item it = decode_item(local, lv.tiles, bq.m.A);
+        if constexpr (PHASE == 0)
+          stats_item(bq.m, lv, it, smem, sh);
+        else if (!leaf)
           update_item(bq.m, lv, it, smem, sh);
         else
           leaf_item<APAD>(bq.m, lv, bq.tr, it, smem, sh);
-      } else {
-        const int local = i - bl.base[q];
-        leaf_parent_item<APAD, -1, kLeafBlock>(bq.m, lv, bq.tr, local / lv.tiles, local % lv.tiles,
-                                               smem, shl);
       }
       __syncthreads();
     }
+    // the wait is spelt out: the compiler leaves that of the barrier at the top
+    // out on this way round the loop, and wavefronts would part with
+    // different items
+    if (threadIdx.x == 0) s_item = next;
+    wait_lds();
   }
 }
 
@@ -3234,25 +3293,24 @@ hipError_t launch_batch_prep(const BatchPrep &bp, int cell_blocks, int lm_blocks
   return hipGetLastError();
 }
 
+size_t stats_parent_lds_bytes(int W, int TH, int L) {
+  return stats_parent_lds_floats(W, TH, L) * sizeof(float);
+}
+
 size_t leaf_parent_lds_bytes(int W, int TH, int L, int AM) {
   return leaf_parent_lds_floats(W, TH, L, AM) * sizeof(float);
 }
 
-template <int PHASE, int APAD>
-static const void *level_kernel() {
-  return (const void *)k_level_batch<PHASE, APAD>;
+// The kernel of a phase (pp: per-parent items in phases 0 and 1).
+static const void *batch_kernel_ptr(int phase, int apad, bool pp) {
+  if (phase == 0) return pp ? (const void *)k_level_batch<0, 4, true> : (const void *)k_level_batch<0, 4, false>;
+  if (phase == 2) return apad <= 4 ? (const void *)k_level_batch<2, 4, false> : (const void *)k_level_batch<2, 8, false>;
+  if (apad <= 8) return pp ? (const void *)k_level_batch<1, 8, true> : (const void *)k_level_batch<1, 8, false>;
+  return pp ? (const void *)k_level_batch<1, 16, true> : (const void *)k_level_batch<1, 16, false>;
 }
 
-static const void *batch_kernel_ptr(int phase, int apad) {
-  if (phase == 0) return level_kernel<0, 4>();
-  if (phase == 2) return apad <= 4 ? level_kernel<2, 4>() : level_kernel<2, 8>();
-  if (apad <= 4) return level_kernel<1, 4>();
-  if (apad <= 8) return level_kernel<1, 8>();
-  return level_kernel<1, 16>();
-}
-
-int batch_level_occupancy(int phase, int apad, size_t lds) {
-  const void *k = batch_kernel_ptr(phase, apad);
+int batch_level_occupancy(int phase, int apad, size_t lds, bool pp) {
+  const void *k = batch_kernel_ptr(phase, apad, pp);
   if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
     return 0;
   int nb = 0;
@@ -3263,21 +3321,25 @@ int batch_level_occupancy(int phase, int apad, size_t lds) {
 }
 
 hipError_t launch_batch_level(const BatchLevel &bl, int phase, int apad, size_t lds, int grid,
-                              hipStream_t st, bool timed) {
+                              bool pp, hipStream_t st, bool timed) {
   if (grid <= 0) return hipSuccess;
   const int d = bl.d;
-  if (phase == 0) {
-    QV_LAUNCH_T(timed, d, (k_level_batch<0, 4>), dim3(grid), dim3(kBlock), lds, st, bl);
+  if (phase == 0 && pp) {
+    QV_LAUNCH_T(timed, d, (k_level_batch<0, 4, true>), dim3(grid), dim3(kBlock), lds, st, bl);
+  } else if (phase == 0) {
+    QV_LAUNCH_T(timed, d, (k_level_batch<0, 4, false>), dim3(grid), dim3(kBlock), lds, st, bl);
   } else if (phase == 2 && apad <= 4) {
-    QV_LAUNCH_T(timed, d, (k_level_batch<2, 4>), dim3(grid), dim3(kLeafBlock), lds, st, bl);
+    QV_LAUNCH_T(timed, d, (k_level_batch<2, 4, false>), dim3(grid), dim3(kLeafBlock), lds, st, bl);
   } else if (phase == 2) {
-    QV_LAUNCH_T(timed, d, (k_level_batch<2, 8>), dim3(grid), dim3(kLeafBlock), lds, st, bl);
-  } else if (apad <= 4) {
-    QV_LAUNCH_T(timed, d, (k_level_batch<1, 4>), dim3(grid), dim3(kBlock), lds, st, bl);
+    QV_LAUNCH_T(timed, d, (k_level_batch<2, 8, false>), dim3(grid), dim3(kLeafBlock), lds, st, bl);
+  } else if (apad <= 8 && pp) {
+    QV_LAUNCH_T(timed, d, (k_level_batch<1, 8, true>), dim3(grid), dim3(kBlock), lds, st, bl);
   } else if (apad <= 8) {
-    QV_LAUNCH_T(timed, d, (k_level_batch<1, 8>), dim3(grid), dim3(kBlock), lds, st, bl);
+    QV_LAUNCH_T(timed, d, (k_level_batch<1, 8, false>), dim3(grid), dim3(kBlock), lds, st, bl);
+  } else if (pp) {
+    QV_LAUNCH_T(timed, d, (k_level_batch<1, 16, true>), dim3(grid), dim3(kBlock), lds, st, bl);
   } else {
-    QV_LAUNCH_T(timed, d, (k_level_batch<1, 16>), dim3(grid), dim3(kBlock), lds, st, bl);
+    QV_LAUNCH_T(timed, d, (k_level_batch<1, 16, false>), dim3(grid), dim3(kBlock), lds, st, bl);
   }
   return hipGetLastError();
 }
