@@ -195,4 +195,10 @@ __device__ __forceinline__ int fdiv(int i, int d, float rd) {
   return q;
 }
 
+// Floor division of 0 <= i < 2^21 by 1 <= d < 2^14, rd = 1.0f / d: (i + 1/2) / d
+// is at least 1/(2d) from a whole number, the error below i 2^-23 / d.
+__device__ __forceinline__ int row_of(int i, float rd) {
+  return (int)fmaf((float)i, rd, 0.5f * rd);
+}
+
 }  // namespace qv

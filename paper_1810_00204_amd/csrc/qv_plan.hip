@@ -456,43 +456,66 @@ hipError_t launch_prep_lm(const DevModel &dm, uint32_t *sig, float *staytab, int
 // zero mass in every belief the library forms; with `mask` (the caller's
 // start belief) they are zeroed here as well.  Loads are issued in batches
 // so that each thread has several in flight.
+// A wavefront takes a piece of a row (64 cells) or, on grids of at most 32
+// columns, 64 / W rows at a time: consecutive cells, so what a lane needs
+// per load is its offset and one compare for the grid's edge: 28 instructions
+// an entry with a division by the padded width, 14 so.  (The same with the
+// rows and pieces worked out in scalar registers and a branch per piece: fewer
+// vector instructions still, but the plan of 512 x 512 took 824 us, not 806.)
 constexpr int kBandBatch = 8;
 template <int BATCH = kBandBatch, int NT = kBlock>
 __device__ __forceinline__ void load_band(const DevModel &m, const uint32_t *sig,
                                           const float *b, int y0, int th, float *band,
                                           int BW, bool mask) {
-  const int n = (th + 2) * BW;
-  const float rBW = 1.0f / (float)BW;
-  for (int i0 = threadIdx.x; i0 < n; i0 += BATCH * NT) {
-    int cell[BATCH];
+  constexpr int NW = NT / kWave;
+  const int W = m.W, rows = th + 2;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int q = W <= kWave / 2 ? kWave / W : 1;   // rows of a piece
+  const int nc = (W + kWave - 1) / kWave;         // pieces of a row (1 where q > 1)
+  const int lr = q > 1 ? lane / W : 0;
+  // piece u: rows q (u / nc) on, cells 64 (u mod nc) on; the division as a
+  // product: exact for u nc < 2^19, and a band has at most 2^11 pieces, nc 2^8
+  const int inv = __builtin_amdgcn_readfirstlane((int)((float)(1 << 20) / (float)nc)) + 1;
+  const int nu = (rows + q - 1) / q * nc;
+  const int lo = max(0, y0 - 1) * W, hi = min(m.H, y0 + th + 1) * W;   // cells on the grid
+  for (int i = threadIdx.x; i < 2 * rows; i += NT) band[(i >> 1) * BW + ((i & 1) ? W + 1 : 0)] = 0.f;
+  for (int u0 = wave; u0 < nu; u0 += BATCH * NW) {
+    int t[BATCH];
     float v[BATCH];
 #pragma unroll
     for (int j = 0; j < BATCH; ++j) {
-      const int i = i0 + j * NT;
-      const int r = fdiv(i, BW, rBW);
-      const int gy = y0 - 1 + r, gx = i - r * BW - 1;
-      const bool in = i < n && gy >= 0 && gy < m.H && gx >= 0 && gx < m.W;
-      cell[j] = in ? gy * m.W + gx : -1;
-      // every lane loads (cell 0 for halo and padding lanes), so the loads of
-      // the batch go out together without a branch around each
-      // (bitwise conditions: a short-circuit one lets the compiler move the
-      // load under a branch)
-      const float bv = b[in ? cell[j] : 0];
-      v[j] = ((uint32_t)in & (uint32_t)(cell[j] != m.goal)) ? bv : 0.f;
+      const int u = min(u0 + j * NW, nu - 1), r = (u * inv) >> 20, c = u - r * nc;
+      t[j] = (y0 - 1 + r * q) * W + c * kWave + lane;
+      t[j] = (uint32_t)(t[j] - lo) < (uint32_t)(hi - lo) ? t[j] : -1;
+      // every lane loads (cell 0 off the grid), so the loads of the batch go
+      // out together without a branch around each
+      v[j] = b[max(t[j], 0)];
     }
+#pragma unroll
+    for (int j = 0; j < BATCH; ++j)
+      v[j] = ((uint32_t)(t[j] >= 0) & (uint32_t)(t[j] != m.goal)) ? v[j] : 0.f;
     if (mask) {
 #pragma unroll
       for (int j = 0; j < BATCH; ++j) {
-        const uint32_t sv = sig[cell[j] >= 0 ? cell[j] : 0];
-        v[j] = ((uint32_t)(cell[j] >= 0) & (sv ^ kSigFree) & kSigFree) ? 0.f : v[j];
+        const uint32_t sv = sig[max(t[j], 0)];
+        v[j] = (sv & kSigFree) ? v[j] : 0.f;
       }
     }
 #pragma unroll
     for (int j = 0; j < BATCH; ++j) {
-      const int i = i0 + j * NT;
-      if (i < n) band[i] = v[j];
+      const int u = u0 + j * NW;
+      if (u >= nu) break;
+      const int r = (u * inv) >> 20, c = u - r * nc;
+      if (lane < q * W - c * kWave && r * q + lr < rows)
+        band[r * q * BW + 1 + c * kWave + lane + 2 * lr] = v[j];
     }
   }
+}
+
+// Place in the band of its i-th cell (row-major, without halo).
+__device__ __forceinline__ int band_pos(int i, float rW, int BW) {
+  return i + 2 * row_of(i, rW) + BW + 1;
 }
 
 // b'(t) for cell t = (y0+ly)*W + lx of the band.
@@ -571,8 +594,8 @@ __device__ __forceinline__ void load_q_row(const LevelArgs &lv, int A, int t, fl
 
 // Sum of x[k * stride] over lo <= k < hi in a fixed order: eight running
 // sums over k - lo mod 8, then added pairwise.  The last partial group loads
-// all eight slots (x[0] in place of those past hi) and masks them, so its
-// loads go out together.
+// eight slots (its last one again past hi) and masks them, so its loads go
+// out together.
 __device__ __forceinline__ float range_sum(const float *x, int stride, int lo, int hi) {
   float s[8];
 #pragma unroll
@@ -581,11 +604,36 @@ __device__ __forceinline__ float range_sum(const float *x, int stride, int lo, i
   for (; k + 8 <= hi; k += 8)
 #pragma unroll
     for (int u = 0; u < 8; ++u) s[u] += x[(k + u) * stride];
-  float t[8];
+  if (k < hi) {
+    float t[8];
 #pragma unroll
-  for (int u = 0; u < 8; ++u) t[u] = x[(k + u < hi ? k + u : 0) * stride];
+    for (int u = 0; u < 8; ++u) t[u] = x[min(k + u, hi - 1) * stride];
 #pragma unroll
-  for (int u = 0; u < 8; ++u) s[u] += (k + u < hi) ? t[u] : 0.f;
+    for (int u = 0; u < 8; ++u) s[u] += (k + u < hi) ? t[u] : 0.f;
+  }
+  return ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+}
+
+// range_sum where lo and hi are the same for the whole wavefront (and held in
+// scalar registers): no lane waits for another's range.
+template <int STRIDE>
+__device__ __forceinline__ float range_sum_wave(const float *x, int lo, int hi) {
+  float s[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) s[u] = 0.f;
+  int k = lo;
+  for (; k + 8 <= hi; k += 8) {
+    const float *xk = x + k * STRIDE;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s[u] += xk[u * STRIDE];
+  }
+  if (k < hi) {
+    float t[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) t[u] = x[min(k + u, hi - 1) * STRIDE];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s[u] += (k + u < hi) ? t[u] : 0.f;
+  }
   return ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
 }
 
@@ -1992,9 +2040,17 @@ __global__ __launch_bounds__(LEAF ? kBlock : kNodeBlock) void k_node(DevModel m,
 // parallel, and the workgroup forms the leaf and Q-node values, the node value
 // and the backup towards the root.
 // ---------------------------------------------------------------------------
-constexpr int kLeafParentBatch = 2;   // sorted cells whose loads go out together
+// What bounds it: the vector ALU's instruction count, about one a clock and CU
+// at two workgroups a CU (register-bound).  A cell costs 133 (81 of them the
+// basis sums, A = 8); around them an item costs as much again in loading the
+// band, sorting out lanes and summing histograms, so those go without
+// divisions, with ranges held in scalar registers, and a wavefront per sum.
+// Measured, 512 x 512, 8 actions, 600 parents x 32 bands (VALU instructions;
+// the whole plan): 464 million, 887 us -> 312 million, 772 us.
 constexpr int kLeafBlock = 2 * kBlock;   // threads of a k_leaf_parent workgroup
-constexpr int kLeafBasisRound = 5;    // basis sums (values of k) per histogram round (two rounds)
+// basis sums (values of k) per histogram round: all nine where a thread's
+// values fit the lanes of a wavefront (A <= 4), else two rounds
+__host__ __device__ constexpr int leaf_basis_round(int AM) { return AM <= 4 ? 9 : 5; }
 constexpr int kLeafPiece = 16;        // chunks per piece of a wall reading's chunk range
 constexpr int kLeafPieces = 32;       // pieces at most: kBlock / kLeafPiece + 15
 static_assert(kBlock / kLeafPiece + 15 <= kLeafPieces, "piece table too small");
@@ -2014,19 +2070,18 @@ struct LeafParentShared {
 };
 
 // Floats of dynamic LDS: one region that holds in turn the band, the chunk
-// partials and the landmark tables; then one that holds the predicted masses
-// of the landmark cells during the cell pass and afterwards the basis
-// histograms, the actions' histograms and the piece sums of one round.
+// partials and piece sums of one round, and the landmark tables; then one that
+// holds the predicted masses of the landmark cells during the cell pass and
+// afterwards the basis histograms and the actions' histograms.
 __host__ __device__ inline size_t leaf_parent_lds_floats(int W, int TH, int L, int AM,
                                                         int NT = kLeafBlock) {
   const int NW = NT / kWave;
   const size_t band = (size_t)(TH + 2) * (W + 2);
   const size_t lmk = (size_t)(1 + NW) * L + 32 * NW;   // landmark tables, sampler tables
-  const size_t part = (size_t)kBlock * kLeafBasisRound * (AM + 1);   // chunk partials, one round
+  const size_t part = (size_t)(kBlock + kLeafPieces) * leaf_basis_round(AM) * (AM + 1);   // one round
   size_t x = band > lmk ? band : lmk;
   x = x > part ? x : part;
-  const size_t hist = (size_t)9 * 16 * (AM + 1) + (size_t)AM * 16 * (AM + 1) +
-                     (size_t)kLeafPieces * kLeafBasisRound * (AM + 1);
+  const size_t hist = (size_t)9 * 16 * (AM + 1) + (size_t)AM * 16 * (AM + 1);
   const size_t lmt = (size_t)AM * L;
   return x + (hist > lmt ? hist : lmt);
 }
@@ -2161,17 +2216,15 @@ __host__ __device__ inline size_t leaf_finish_lds_floats(int L, int K, int A, in
 template <int AM, int QV, int NT>
 __device__ void leaf_parent_item(const DevModel &m, const LevelArgs &lv, const TreeArgs &tr,
                                  int p, int band, float *smem, LeafParentShared &sh) {
-  static_assert(NT == kBlock || NT == 2 * kBlock, "one or two threads per chunk");
+  static_assert(NT == 2 * kBlock, "two threads per chunk");
   constexpr int NV = AM + 1;
   constexpr int NW = NT / kWave;            // wavefronts
-  constexpr int HALVES = NT / kBlock;       // threads per sorted chunk
-  // sorted cells whose loads go out together (one at 2 kBlock threads, whose
-  // workgroups must fit in 128 registers for two to share a CU)
-  constexpr int LPB = NT == kBlock ? kLeafParentBatch : 1;
+  constexpr int HALVES = 2;                 // threads per sorted chunk
   constexpr int RECN = AM * 16 * NV + AM;   // band record: HQ, then R(b,a)
   const int A = m.A, W = m.W, BW = W + 2, S = m.S, L = m.L;
   const int K = lv.K;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int wv = __builtin_amdgcn_readfirstlane(wave);   // the same, known to be uniform
   if (!lv.pvalid[p]) {
     // children of an absent parent are absent (marked by k_leaf_finish when
     // it completes the parents); the parent takes no part in any backup
@@ -2187,19 +2240,27 @@ __device__ void leaf_parent_item(const DevModel &m, const LevelArgs &lv, const T
   }
   const int TH = lv.TH, y0 = band * TH, th = min(TH, m.H - y0);
   const size_t bandf = (size_t)(TH + 2) * BW, lmkf = (size_t)(1 + NW) * L + 32 * NW;
-  const size_t partf = (size_t)kBlock * kLeafBasisRound * NV;
+  // the chunk partials of a round, then the piece sums
+  const size_t partf = (size_t)(kBlock + kLeafPieces) * leaf_basis_round(AM) * NV;
   const size_t xf = bandf > lmkf ? (bandf > partf ? bandf : partf) : (lmkf > partf ? lmkf : partf);
   float *X = smem;             // band, then the chunk partials, then the landmark tables
   float *part = X;             // [kBlock][round values], later the backup scratch
   float *E = smem + xf;        // [9][16][NV] basis histograms
   float *HQ = E + 9 * 16 * NV;   // [AM][16][NV]
-  float *PP = HQ + AM * 16 * NV;   // [piece][round values]
+  float *PP = part + (size_t)kBlock * leaf_basis_round(AM) * NV;   // [piece][round values]
   float *LT = E;                   // [AM][L] b'_a of the landmark cells, during the cell pass
   const float *b = lv.pbel + (size_t)p * S;
   if (tid < AM * 9) sh.slip[tid] = tid < A * 9 ? m.slip[tid] : 0.f;
   if (tid == 0) sh.goal_w = -1;
   // landmarks outside this band keep the mark -1 (predicted masses are >= 0)
   for (int i = tid; i < AM * L; i += NT) LT[i] = -1.f;
+  // chunk ck belongs to the reading w with pch[w] <= ck < pch[w+1]; the
+  // HALVES (pch[w+1] - pch[w]) lanes of reading w take its sorted positions
+  // [rst[w], rst[w+1]) in turn, so a wavefront's loads at one step fall on
+  // consecutive positions (neighbouring cells of one reading).  Lane v < 17
+  // holds pch[v], lane 17 + v rst[v].
+  const int32_t *ch = lv.sort_chunk + (size_t)band * kSortChunkInts;
+  const int starts = ch[2 * kBlock + min(lane, 33)];
   load_band<24 * kBlock / NT, NT>(m, lv.sig, b, y0, th, X, BW, lv.d == 0);
   __syncthreads();
   const float rho = m.lm_p;
@@ -2239,8 +2300,7 @@ __device__ void leaf_parent_item(const DevModel &m, const LevelArgs &lv, const T
           }
         }
         const int ic = i < ncell ? i : 0;
-        const int ly = fdiv(ic, W, rW);
-        const float xv = X[(ly + 1) * BW + (ic - ly * W) + 1];
+        const float xv = X[band_pos(ic, rW, BW)];
         bb[k] = (i < ncell) ? ((t == m.goal) ? bgoal : xv) : 0.f;
       }
 #pragma unroll
@@ -2249,10 +2309,12 @@ __device__ void leaf_parent_item(const DevModel &m, const LevelArgs &lv, const T
         for (int a = 0; a < AM; ++a) racc[a] = fmaf(bb[k], r4[k][a], racc[a]);
     }
   }
+  if (lv.own_reward) {
 #pragma unroll
-  for (int a = 0; a < AM; ++a) {
-    const float tot = wave_total_lane63(racc[a]);
-    if (lane == kWave - 1) sh.red[wave][a] = tot;
+    for (int a = 0; a < AM; ++a) {
+      const float tot = wave_total_lane63(racc[a]);
+      if (lane == kWave - 1) sh.red[wave][a] = tot;
+    }
   }
   // basis sums E_k[c] of this thread's cells of its chunk (one wall reading)
   float acc[9][NV];
@@ -2260,23 +2322,15 @@ __device__ void leaf_parent_item(const DevModel &m, const LevelArgs &lv, const T
   for (int k = 0; k < 9; ++k)
 #pragma unroll
     for (int c = 0; c < NV; ++c) acc[k][c] = 0.f;
-  const int32_t *ch = lv.sort_chunk + (size_t)band * kSortChunkInts;
-  // chunk ck belongs to the reading w with pch[w] <= ck < pch[w+1]; the
-  // HALVES (pch[w+1] - pch[w]) lanes of reading w take its sorted positions
-  // [rst[w], rst[w+1]) in turn, so a wavefront's loads at one step fall on
-  // consecutive positions (neighbouring cells of one reading)
   const int ck = tid / HALVES, half = tid % HALVES;
-  const int32_t *pchk = ch + 2 * kBlock, *rst = pchk + 17;
-  int lo = 0, hi = 0, cfirst = 0, nch = 1;
+  int rd = 0;   // the reading
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int a0 = pchk[v], a1 = pchk[v + 1], r0 = rst[v], r1 = rst[v + 1];
-    const bool mine = (ck >= a0) & (ck < a1);
-    lo = mine ? r0 : lo;
-    hi = mine ? r1 : hi;
-    cfirst = mine ? a0 : cfirst;
-    nch = mine ? a1 - a0 : nch;
-  }
+  for (int v = 1; v < 16; ++v) rd += ck >= __builtin_amdgcn_readlane(starts, v) ? 1 : 0;
+  const int cfirst = __shfl(starts, rd, kWave), cend = __shfl(starts, rd + 1, kWave);
+  const bool mine = ck < cend;   // false past the last chunk
+  const int plo = __shfl(starts, 17 + rd, kWave), phi = __shfl(starts, 18 + rd, kWave);
+  const int lo = mine ? plo : 0, hi = mine ? phi : 0;
+  const int nch = mine ? cend - cfirst : 1;
   const int sd = HALVES * nch;   // between one lane's positions
   const int j0 = lo + (ck - cfirst) * HALVES + half, j1 = hi;
   if (wave == NW - 1 && lane < 16) {
@@ -2299,175 +2353,167 @@ __device__ void leaf_parent_item(const DevModel &m, const LevelArgs &lv, const T
       sh.pc_hi[pf + j] = min(c0 + (j + 1) * kLeafPiece, c1);
     }
   }
-  // the lane's positions in batches, software-pipelined: while a batch is
-  // computed, the next batch's Q rows and the entries of the one after are
-  // in flight; positions past the reading read a valid entry and are masked
-  // to zero, so the loads need no branch
+  // the lane's positions, software-pipelined: while one is computed, the next
+  // one's Q row and the entry of the one after are in flight; past the
+  // reading its last entry is read again, so the loads need no branch
   const int jmax = max(j1 - 1, 0);
-  const int STEP = LPB * sd;
-  uint32_t en[LPB], en2[LPB];
-  float qn[LPB][AM];
+  auto entry = [&](int j) {
+    return *(const uint32_t *)((const char *)lv.sort_cells + (uint32_t)min(j, jmax) * 4u);
+  };
+  const int c0 = BW + 1 - y0 * W;
+  auto cell = [&](uint32_t e, const float (&q)[AM]) {
+    const int t = (int)(e & kSortCell);
+    const float *c = X + (t + c0) + 2 * row_of(t - y0 * W, rW);
+    const float self = c[0];
+    // s_k: the mass that move k brings to x (from the neighbour at -d_k),
+    // plus x's own mass when move k is blocked at x (bit clear in the
+    // 8-neighbour pattern); s_4 = b(x)
+    const uint32_t blk = ~e;
+    float s[9];
+    s[0] = c[BW + 1];
+    s[1] = c[BW];
+    s[2] = c[BW - 1];
+    s[3] = c[1];
+    s[4] = self;
+    s[5] = c[-1];
+    s[6] = c[-BW + 1];
+    s[7] = c[-BW];
+    s[8] = c[-BW - 1];
 #pragma unroll
-  for (int k = 0; k < LPB; ++k) {
-    const int jk = j0 + k * sd, jk2 = jk + STEP;
-    const uint32_t v = (uint32_t)lv.sort_cells[min(jk, jmax)];
-    const uint32_t v2 = (uint32_t)lv.sort_cells[min(jk2, jmax)];
-    en[k] = jk < j1 ? v : 0u;
-    en2[k] = jk2 < j1 ? v2 : 0u;
-  }
-#pragma unroll
-  for (int k = 0; k < LPB; ++k) load_q_row<AM, QV>(lv, A, (int)(en[k] & kSortCell), qn[k]);
-  for (int j = j0; j < j1; j += STEP) {
-    uint32_t e[LPB];
-    float q[LPB][AM];
-#pragma unroll
-    for (int k = 0; k < LPB; ++k) {
-      e[k] = en[k];
-#pragma unroll
-      for (int c = 0; c < AM; ++c) q[k][c] = qn[k][c];
-      en[k] = en2[k];
-      load_q_row<AM, QV>(lv, A, (int)(en[k] & kSortCell), qn[k]);
+    for (int kk = 0; kk < 9; ++kk) {
+      if (kk == 4) continue;
+      const int bit = kSortOutShift + (kk < 4 ? kk : kk - 1);
+      const int on = (int)(blk << (31 - bit)) >> 31;   // all ones where the move is blocked
+      s[kk] += __int_as_float(on & __float_as_int(self));
     }
+    if (e >= kSortGoal) {   // the goal or a landmark cell
+      // b'_a(x) = sum_k T'(a,k) s_k(x): the predicted mass on a landmark
+      // cell (for its observation) and on the goal, where the band holds
+      // zero (s_k is the inflow only) and the own mass stays with weight 1
+      const bool goal = (e & kSortGoal) != 0, lmk = (e & kSortLandmark) != 0;
+      const uint32_t sg = lv.sig[t];
+      const uint32_t lid = sig_lm(sg);
+      const float lg = lmk ? 1.f - rho : 1.f;
+      for (int a = 0; a < A; ++a) {
+        float v = 0.f;
 #pragma unroll
-    for (int k = 0; k < LPB; ++k) {
-      const int jn = j + 2 * STEP + k * sd;
-      const uint32_t v = (uint32_t)lv.sort_cells[min(jn, jmax)];
-      en2[k] = jn < j1 ? v : 0u;
-    }
-    // every lane runs the whole batch: a slot past its chunk's end reads the
-    // band's first cell with weight zero
+        for (int kk = 0; kk < 9; ++kk) v = fmaf(sh.slip[a * 9 + kk], s[kk], v);
+        if (goal) {
+          v += bgoal;
+          const float gv = lg * v;
+          sh.goal[a * NV + AM] = gv;
 #pragma unroll
-    for (int k = 0; k < LPB; ++k) {
-      const bool in = j + k * sd < j1;
-      const int t = in ? (int)(e[k] & kSortCell) : y0 * W;
-      const int gy = fdiv(t, W, rW);
-      const float *c = X + (gy - y0 + 1) * BW + (t - gy * W) + 1;
-      const float self = c[0];
-      // s_k: the mass that move k brings to x (from the neighbour at -d_k),
-      // plus x's own mass when move k is blocked at x (bit clear in the
-      // 8-neighbour pattern); s_4 = b(x)
-      const uint32_t o8 = (e[k] >> kSortOutShift) & 0xFFu;
-      float s[9];
-      s[0] = c[BW + 1];
-      s[1] = c[BW];
-      s[2] = c[BW - 1];
-      s[3] = c[1];
-      s[4] = self;
-      s[5] = c[-1];
-      s[6] = c[-BW + 1];
-      s[7] = c[-BW];
-      s[8] = c[-BW - 1];
-#pragma unroll
-      for (int kk = 0; kk < 9; ++kk) {
-        if (kk == 4) continue;
-        const int bit = kk < 4 ? kk : kk - 1;
-        s[kk] += ((o8 >> bit) & 1u) ? 0.f : self;
-      }
-      const bool goal = (e[k] & kSortGoal) != 0;
-      const bool lmk = (e[k] & kSortLandmark) != 0;
-      const float lam = (in && !goal) ? (lmk ? 1.f - rho : 1.f) : 0.f;
-#pragma unroll
-      for (int kk = 0; kk < 9; ++kk) {
-        const float v = s[kk] * lam;
-#pragma unroll
-        for (int cc = 0; cc < AM; ++cc) acc[kk][cc] = fmaf(v, q[k][cc], acc[kk][cc]);
-        acc[kk][AM] += v;
-      }
-      if (in && (lmk || goal)) {
-        // b'_a(x) = sum_k T'(a,k) s_k(x): the predicted mass on a landmark
-        // cell (for its observation) and on the goal, where the band holds
-        // zero (s_k is the inflow only) and the own mass stays with weight 1
-        const uint32_t sg = lv.sig[t];
-        const uint32_t lid = sig_lm(sg);
-        const float lg = lmk ? 1.f - rho : 1.f;
-        for (int a = 0; a < A; ++a) {
-          float v = 0.f;
-#pragma unroll
-          for (int kk = 0; kk < 9; ++kk) v = fmaf(sh.slip[a * 9 + kk], s[kk], v);
-          if (goal) {
-            v += bgoal;
-            const float gv = lg * v;
-            sh.goal[a * NV + AM] = gv;
-#pragma unroll
-            for (int cc = 0; cc < AM; ++cc) sh.goal[a * NV + cc] = gv * q[k][cc];
-          }
-          if (lmk) LT[a * L + lid - 1] = v;
+          for (int cc = 0; cc < AM; ++cc) sh.goal[a * NV + cc] = gv * q[cc];
         }
-        if (goal) sh.goal_w = (int)sig_wall(sg);
+        if (lmk) LT[a * L + lid - 1] = v;
       }
+      if (goal) sh.goal_w = (int)sig_wall(sg);
+      // the weight in the histograms: the "no landmark" factor, none of the goal
+      const float lam = goal ? 0.f : lg;
+#pragma unroll
+      for (int kk = 0; kk < 9; ++kk) s[kk] *= lam;
     }
+#pragma unroll
+    for (int kk = 0; kk < 9; ++kk) {
+#pragma unroll
+      for (int cc = 0; cc < AM; ++cc) acc[kk][cc] = fmaf(s[kk], q[cc], acc[kk][cc]);
+      acc[kk][AM] += s[kk];
+    }
+  };
+  uint32_t ea = entry(j0), eb = entry(j0 + sd);
+  float qa[AM], qb[AM];
+  load_q_row<AM, QV>(lv, A, (int)(ea & kSortCell), qa);
+  for (int j = j0; j < j1; j += sd) {
+    load_q_row<AM, QV>(lv, A, (int)(eb & kSortCell), qb);
+    const uint32_t ec = entry(j + 2 * sd);
+    cell(ea, qa);
+    j += sd;
+    if (j >= j1) break;
+    load_q_row<AM, QV>(lv, A, (int)(ec & kSortCell), qa);
+    ea = ec;
+    const uint32_t ed = entry(j + 2 * sd);
+    cell(eb, qb);
+    eb = ed;
   }
-  // chunk partials -> basis histograms by wall reading, kLeafBasisRound
-  // values of k per round: one thread per (piece, value) adds the piece's
-  // chunk partials in chunk order, then one thread per (reading, value) adds
-  // the reading's piece sums in piece order (range_sum)
-  constexpr int G = kLeafBasisRound;
+  // chunk partials -> basis histograms by wall reading, leaf_basis_round(AM)
+  // values of k per round: a wavefront takes a piece, a lane a value, and adds
+  // the piece's chunk partials in chunk order; then a wavefront takes a reading
+  // and adds its piece sums in piece order.  (Pieces and readings dealt to
+  // single threads, the lanes of a wavefront had different ranges and each
+  // its own index arithmetic: a third of this kernel's instructions.)
+  constexpr int G = leaf_basis_round(AM);
   constexpr int GW = G * NV;          // floats per thread and round
+  static_assert(GW <= kWave, "a lane per value");
   __syncthreads();                    // the band is read no more: part takes its place
   // the landmark cells' predicted masses go out to lmv (the sampler of this
   // or, with several bands, the last band reads them); kept in LDS during the
   // cell pass, so no store waits there
   for (int i = tid; i < A * L; i += NT) {
-    const int a = i / L, l = i - a * L;
-    const float v = LT[a * L + l];
-    if (v >= 0.f) st_coherent(lv.lmv + ((size_t)p * A + a) * L + l, v);
+    const float v = LT[i];
+    if (v >= 0.f) st_coherent(lv.lmv + (size_t)p * A * L + i, v);
   }
 #pragma unroll
   for (int k0 = 0; k0 < 9; k0 += G) {
-    if constexpr (HALVES == 2) {
-      // a chunk's two lanes add their sums on the DPP network (both get the
-      // same bits: addition commutes), then store alternate values
+    // a chunk's two lanes add their sums on the DPP network (both get the
+    // same bits: addition commutes), then store alternate values
 #pragma unroll
-      for (int gi = 0; gi < GW; gi += 2) {
-        const int g0 = gi / NV, c0 = gi % NV, g1 = (gi + 1) / NV, c1 = (gi + 1) % NV;
-        if (k0 + g0 < 9) {
-          float v0 = acc[k0 + g0][c0];
-          v0 += dpp_xor1(v0);
-          if (gi + 1 < GW && k0 + g1 < 9) {
-            float v1 = acc[k0 + g1][c1];
-            v1 += dpp_xor1(v1);
-            part[ck * GW + gi + half] = half ? v1 : v0;
-          } else {
-            part[ck * GW + gi] = v0;   // both lanes write the same value
-          }
+    for (int gi = 0; gi < GW; gi += 2) {
+      const int g0 = gi / NV, c0 = gi % NV, g1 = (gi + 1) / NV, c1 = (gi + 1) % NV;
+      if (k0 + g0 < 9) {
+        float v0 = acc[k0 + g0][c0];
+        v0 += dpp_xor1(v0);
+        if (gi + 1 < GW && k0 + g1 < 9) {
+          float v1 = acc[k0 + g1][c1];
+          v1 += dpp_xor1(v1);
+          part[ck * GW + gi + half] = half ? v1 : v0;
+        } else {
+          part[ck * GW + gi] = v0;   // both lanes write the same value
         }
       }
-    } else {
-#pragma unroll
-      for (int gi = 0; gi < GW; ++gi)
-        if (k0 + gi / NV < 9) part[ck * GW + gi] = acc[k0 + gi / NV][gi % NV];
     }
     __syncthreads();
-    const int npc = sh.pfirst[16];
-    for (int i = tid; i < npc * GW; i += NT) {
-      const int pc = i / GW, gi = i - pc * GW;
-      if (k0 + gi / NV < 9) PP[i] = range_sum(part + gi, GW, sh.pc_lo[pc], sh.pc_hi[pc]);
+    const int npc = __builtin_amdgcn_readfirstlane(sh.pfirst[16]);
+    const bool on = lane < GW && k0 + lane / NV < 9;
+    for (int pc = wv; pc < npc; pc += NW) {
+      const int c0 = __builtin_amdgcn_readfirstlane(sh.pc_lo[pc]);
+      const int c1 = __builtin_amdgcn_readfirstlane(sh.pc_hi[pc]);
+      if (on) PP[pc * GW + lane] = range_sum_wave<GW>(part + lane, c0, c1);
     }
     __syncthreads();
-    for (int i = tid; i < 16 * GW; i += NT) {
-      const int w = i / GW, gi = i - w * GW;
-      const int g = gi / NV, c = gi - g * NV;
-      if (k0 + g < 9) E[((k0 + g) * 16 + w) * NV + c] = range_sum(PP + gi, GW, sh.pfirst[w], sh.pfirst[w + 1]);
+    for (int w = wv; w < 16; w += NW) {
+      const int p0 = __builtin_amdgcn_readfirstlane(sh.pfirst[w]);
+      const int p1 = __builtin_amdgcn_readfirstlane(sh.pfirst[w + 1]);
+      if (on)
+        E[((k0 + lane / NV) * 16 + w) * NV + lane % NV] = range_sum_wave<GW>(PP + lane, p0, p1);
     }
     __syncthreads();
   }
   // the actions' histograms HQ_a = sum_k T'(a,k) E_k (k in order), plus the
   // goal's own term on its reading
-  for (int i = tid; i < AM * 16 * NV; i += NT) {
-    const int a = i / (16 * NV), wc = i - a * 16 * NV;
-    float v = 0.f;
-    if (a < A) {
+  // (a thread takes one (w,c) of every NT / (16 NV)-th action)
+  constexpr int NA = NT / (16 * NV);
+  if (tid < NA * 16 * NV) {
+    const int a0 = tid / (16 * NV), wc = tid - a0 * 16 * NV;
+    float ek[9];
 #pragma unroll
-      for (int k = 0; k < 9; ++k) v = fmaf(sh.slip[a * 9 + k], E[k * 16 * NV + wc], v);
-      if (wc / NV == sh.goal_w) v += sh.goal[a * NV + wc % NV];
+    for (int k = 0; k < 9; ++k) ek[k] = E[k * 16 * NV + wc];
+    const bool goal = wc / NV == sh.goal_w;
+#pragma unroll
+    for (int a = a0; a < AM; a += NA) {
+      float v = 0.f;
+      if (a < A) {
+#pragma unroll
+        for (int k = 0; k < 9; ++k) v = fmaf(sh.slip[a * 9 + k], ek[k], v);
+        if (goal) v += sh.goal[a * NV + wc % NV];
+      }
+      HQ[a * 16 * NV + wc] = v;
     }
-    HQ[i] = v;
   }
   __syncthreads();
   if (tid < A) {
     float r8[NW];
 #pragma unroll
-    for (int w = 0; w < NW; ++w) r8[w] = sh.red[w][tid];
+    for (int w = 0; w < NW; ++w) r8[w] = lv.own_reward ? sh.red[w][tid] : 0.f;
     sh.rb[tid] = sum_waves<NW>(r8);
   }
   __syncthreads();
