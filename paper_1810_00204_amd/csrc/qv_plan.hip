@@ -518,29 +518,12 @@ __device__ __forceinline__ int band_pos(int i, float rW, int BW) {
   return i + 2 * row_of(i, rW) + BW + 1;
 }
 
-// b'(t) for cell t = (y0+ly)*W + lx of the band.
-__device__ __forceinline__ float predict_cell(const float *band, int BW, int ly, int lx,
-                                              uint32_t sg, const float *sl,
-                                              const float *stay_a, const float *b, int t) {
-  if (!(sg & kSigFree)) return 0.f;
-  const float *c = band + (ly + 1) * BW + lx + 1;
-  float stay, self;
-  if (sg & kSigGoal) {
-    stay = 1.f;
-    self = b[t];
-  } else {
-    stay = stay_a[sig_out8(sg)];
-    self = c[0];
-  }
-  return stencil(c, BW, sl, stay, self);
-}
-
-// As predict_cell with b(t) already loaded (bt).
-__device__ __forceinline__ float predict_cell_v(const float *band, int BW, int ly, int lx,
+// b'(t) of the cell at `pos` of the band; sg its map signature, bt = b(t).
+__device__ __forceinline__ float predict_cell_v(const float *band, int BW, int pos,
                                                 uint32_t sg, const float *sl,
                                                 const float *stay_a, float bt) {
   if (!(sg & kSigFree)) return 0.f;
-  const float *c = band + (ly + 1) * BW + lx + 1;
+  const float *c = band + pos;
   if (sg & kSigGoal) return stencil(c, BW, sl, 1.f, bt);
   return stencil(c, BW, sl, stay_a[sig_out8(sg)], c[0]);
 }
@@ -1111,8 +1094,7 @@ __device__ void stats_item(const DevModel &m, const LevelArgs &lv, Item it, floa
       if (i >= ncell) break;
       // R(b,a) = sum_x R(x,a) b(x) (Sec. III)
       racc = fmaf(bt[j], rr[j], racc);
-      const int ly = fdiv(i, W, rW), lx = i - ly * W;
-      const float bp = predict_cell_v(band, BW, ly, lx, sg[j], sl, stay_a, bt[j]);
+      const float bp = predict_cell_v(band, BW, band_pos(i, rW, BW), sg[j], sl, stay_a, bt[j]);
       const uint32_t lm = sig_lm(sg[j]);
       float contrib = bp;
       if (lm && lm <= (uint32_t)L) {
@@ -1219,9 +1201,8 @@ __device__ void update_item(const DevModel &m, const LevelArgs &lv, Item it, flo
     for (int j = 0; j < kCellBatch; ++j) {
       const int i = i0 + j * kBlock;
       if (i >= ncell) break;
-      const int ly = fdiv(i, W, rW), lx = i - ly * W;
       const int t = t00 + i;
-      const float bp = predict_cell_v(band, BW, ly, lx, sg[j], sl, stay_a, bt[j]);
+      const float bp = predict_cell_v(band, BW, band_pos(i, rW, BW), sg[j], sl, stay_a, bt[j]);
       const uint32_t w = sig_wall(sg[j]), lm = sig_lm(sg[j]);
 #pragma unroll
       for (int r = 0; r < QV_MAX_SAMPLES; ++r) {
@@ -1346,8 +1327,7 @@ __device__ void stats_parent_item(const DevModel &m, const LevelArgs &lv, int p,
     for (int j = 0; j < kParentCells; ++j) {
       const int i = tid + j * kBlock;
       if (j >= jn || i >= ncell) break;
-      const int ly = fdiv(i, W, rW), lx = i - ly * W;
-      const float bp = predict_cell_v(band, BW, ly, lx, sg[j], sl, stay_a, bt[j]);
+      const float bp = predict_cell_v(band, BW, band_pos(i, rW, BW), sg[j], sl, stay_a, bt[j]);
       const uint32_t lm = sig_lm(sg[j]);
       float contrib = bp;
       if (lm && lm <= (uint32_t)L) {
@@ -1479,8 +1459,7 @@ __device__ void update_parent_item(const DevModel &m, const LevelArgs &lv, int p
 #pragma unroll
       for (int j = 0; j < kCellBatch; ++j) {
         const int i = i0 + j * kBlock;
-        const int ly = fdiv(i, W, rW), lx = i - ly * W;
-        bp[j] = i < ncell ? predict_cell_v(band, BW, ly, lx, sg[j], sl, stay_a, bt[j]) : 0.f;
+        bp[j] = i < ncell ? predict_cell_v(band, BW, band_pos(i, rW, BW), sg[j], sl, stay_a, bt[j]) : 0.f;
       }
       // child by child, so each child's rows of the band go out together
       for (int r = 0; r < U; ++r) {
@@ -1653,8 +1632,7 @@ __device__ void leaf_item(const DevModel &m, const LevelArgs &lv, const TreeArgs
         for (int j = 0; j < kLeafBatch; ++j) {
           const int i = i0 + j * kBlock;
           if (i >= ncell) break;
-          const int ly = fdiv(i, W, rW), lx = i - ly * W;
-          const float bp = predict_cell_v(band, BW, ly, lx, sg[j], sl, stay_a, bt[j]);
+          const float bp = predict_cell_v(band, BW, band_pos(i, rW, BW), sg[j], sl, stay_a, bt[j]);
           const uint32_t w = sig_wall(sg[j]), lm = sig_lm(sg[j]);
 #pragma unroll
           for (int r = 0; r < G; ++r) {
@@ -1825,12 +1803,12 @@ __global__ __launch_bounds__(LEAF ? kBlock : kNodeBlock) void k_node(DevModel m,
     for (int j = 0; j < NBATCH; ++j) {
       const int t = t0 + j * NB;
       if (t < S) {
-        const int ly = fdiv(t, W, rW), lx = t - ly * W;
+        const int pos = band_pos(t, rW, BW);
         // b(t): the band holds the belief (blocked cells hold no mass in any
         // belief the planner accepts or forms), except at the goal
-        const float bt = t == m.goal ? bgoal : band[(ly + 1) * BW + lx + 1];
+        const float bt = t == m.goal ? bgoal : band[pos];
         racc = fmaf(bt, rr[j], racc);
-        const float bp = predict_cell_v(band, BW, ly, lx, sg[j], sl, s_stay, bt);
+        const float bp = predict_cell_v(band, BW, pos, sg[j], sl, s_stay, bt);
         bpl[t] = bp;
         if (!LEAF) {
           const uint32_t lm = sig_lm(sg[j]);
@@ -3560,21 +3538,35 @@ __global__ __launch_bounds__(kBlock) void k_search_expand(DevModel m, SearchArgs
   const float bgoal = m.goal >= 0 ? b[m.goal] : 0.f;
   // b' (slip stencil), R(b,a) and the histogram of b' by true wall reading
   // (landmark cells with their "no landmark" factor), as the level kernels
+  // (the loads of eight cells go out together; then the cells in order)
+  constexpr int NC = 8;
   float racc = 0.f, h0 = 0.f;
-  for (int t = tid; t < S; t += kBlock) {
-    const uint32_t sg = sa.sig[t];
-    const int ly = fdiv(t, W, rW), lx = t - ly * W;
-    const float bt = t == m.goal ? bgoal : band[(ly + 1) * BW + lx + 1];
-    racc = fmaf(bt, m.R[(size_t)t * A + a], racc);
-    const float bp = predict_cell_v(band, BW, ly, lx, sg, sl, s_stay, bt);
-    bpl[t] = bp;
-    const uint32_t lm = sig_lm(sg);
-    const float contrib = (lm && lm <= (uint32_t)m.L) ? bp * (1.f - rho) : bp;
-    const uint32_t w = sig_wall(sg);
-    if (w == 0u)
-      h0 += contrib;
-    else
-      hist[w * kBlock + tid] += contrib;
+  for (int t0 = tid; t0 < S; t0 += NC * kBlock) {
+    uint32_t sg[NC];
+    float rr[NC];
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      const int t = min(t0 + j * kBlock, S - 1);
+      sg[j] = sa.sig[t];
+      rr[j] = m.R[(size_t)t * A + a];
+    }
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      const int t = t0 + j * kBlock;
+      if (t >= S) break;
+      const int pos = band_pos(t, rW, BW);
+      const float bt = t == m.goal ? bgoal : band[pos];
+      racc = fmaf(bt, rr[j], racc);
+      const float bp = predict_cell_v(band, BW, pos, sg[j], sl, s_stay, bt);
+      bpl[t] = bp;
+      const uint32_t lm = sig_lm(sg[j]);
+      const float contrib = (lm && lm <= (uint32_t)m.L) ? bp * (1.f - rho) : bp;
+      const uint32_t w = sig_wall(sg[j]);
+      if (w == 0u)
+        h0 += contrib;
+      else
+        hist[w * kBlock + tid] += contrib;
+    }
   }
   hist[tid] = h0;
   racc = wave_sum(racc);
@@ -3616,8 +3608,88 @@ __global__ __launch_bounds__(kBlock) void k_search_expand(DevModel m, SearchArgs
 // bounds (Alg. 3, Alg. 5) from b'_a, then its records.  Draws left empty
 // return.
 constexpr int kSearchChildBlock = 1024;   // threads of a k_search_child workgroup
+// search_bounds where both tables have at most kSearchRow columns: each
+// wavefront reads the rows of 64 consecutive cells as consecutive words (a lane
+// reading its own row takes a word of a different line each time: 18 lines a
+// load at 9 columns, not 4), turns them in LDS, and has the next 64 cells' rows
+// in flight meanwhile.  The sums are search_bounds' own, in the same order.
+// Measured, 100 x 40, 9 + 9 columns, 27 children: the launch 25 -> 17.7 us.
+// (Wider tables keep search_bounds: their rows would not fit the LDS of 16
+// wavefronts.)
+constexpr int kSearchRow = 12;
+struct SearchRows {
+  float t[kSearchChildBlock / kWave][kWave * kSearchRow];
+};
+__device__ void search_bounds_rows(const DevModel &m, const SearchArgs &sa, const float *bpl,
+                                   int zr, float scale, float *out_b, float *red,
+                                   SearchRows &rows, float &U, float &L) {
+  constexpr int NT = kSearchChildBlock;
+  const int A = m.A, S = m.S, LC = sa.lcols, lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const uint32_t zw = (uint32_t)(zr & 15), zl = (uint32_t)(zr >> 4);
+  float *buf = rows.t[wave];
+  float acc[32];   // values 0..15: the U columns, 16..31: the L columns
+#pragma unroll
+  for (int i = 0; i < 32; ++i) acc[i] = 0.f;
+  uint32_t sg = 0u;
+  float bp = 0.f, ru[kSearchRow], rl[kSearchRow];
+  auto fetch = [&](int t0) {   // t0 < S
+    const int n = min(kWave, S - t0), t = t0 + min(lane, n - 1);
+    sg = sa.sig[t];
+    bp = bpl[t];
+#pragma unroll
+    for (int j = 0; j < kSearchRow; ++j) {
+      if (j < A) ru[j] = (sa.Ut + (size_t)t0 * A)[min(j * kWave + lane, n * A - 1)];
+      if (j < LC) rl[j] = (sa.Lt + (size_t)t0 * LC)[min(j * kWave + lane, n * LC - 1)];
+    }
+  };
+  int t0 = wave * kWave;
+  if (t0 < S) fetch(t0);
+  for (; t0 < S; t0 += NT) {
+    float x[kSearchRow], y[kSearchRow];
+#pragma unroll
+    for (int j = 0; j < kSearchRow; ++j)
+      if (j < A) buf[j * kWave + lane] = ru[j];
+    wait_lds();
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int c = 0; c < kSearchRow; ++c) x[c] = c < A ? buf[lane * A + c] : 0.f;
+    wait_lds();
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int j = 0; j < kSearchRow; ++j)
+      if (j < LC) buf[j * kWave + lane] = rl[j];
+    wait_lds();
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int c = 0; c < kSearchRow; ++c) y[c] = c < LC ? buf[lane * LC + c] : 0.f;
+    wait_lds();
+    __builtin_amdgcn_wave_barrier();
+    const float o = wall_lik(m.flip, zw, sig_wall(sg)) * lm_lik(m.lm_p, zl, sig_lm(sg));
+    const float v = o * bp * scale;
+    const int t = t0 + lane;
+    if (t0 + NT < S) fetch(t0 + NT);
+    if (t < S) {
+      out_b[t] = v;
+#pragma unroll
+      for (int c = 0; c < kSearchRow; ++c) {
+        if (c < A) acc[c] = fmaf(v, x[c], acc[c]);
+        if (c < LC) acc[16 + c] = fmaf(v, y[c], acc[16 + c]);
+      }
+    }
+  }
+  const float tot = block_sum32<NT>(acc, red);
+  if (threadIdx.x < 32) red[threadIdx.x] = tot;
+  __syncthreads();
+  U = -INFINITY;
+  L = -INFINITY;
+  for (int c = 0; c < A; ++c) U = fmaxf(U, red[c]);
+  for (int c = 0; c < LC; ++c) L = fmaxf(L, red[16 + c]);
+}
+
 __global__ __launch_bounds__(kSearchChildBlock) void k_search_child(DevModel m, SearchArgs sa) {
   __shared__ float s_red[kSearchChildBlock / kWave * 32];
+  __shared__ SearchRows s_rows;
   const int a = blockIdx.x / sa.n, r = blockIdx.x - a * sa.n;
   const int v = sa.ctl[kCtlSelect], base = sa.ctl[kCtlNext];
   if (sa.ctl[kCtlFlags] || v < 0 || sa.expanded[v] || base + sa.K > sa.NV) return;
@@ -3626,8 +3698,12 @@ __global__ __launch_bounds__(kSearchChildBlock) void k_search_child(DevModel m, 
   const int S = m.S;
   const int z = sa.z[c];
   float U, L;
-  search_bounds<kSearchChildBlock>(m, sa, sa.bpa + (size_t)a * S, z, 1.0f / sa.pz[c],
-                                   sa.bel + (size_t)c * S, s_red, U, L);
+  if (m.A <= kSearchRow && sa.lcols <= kSearchRow)
+    search_bounds_rows(m, sa, sa.bpa + (size_t)a * S, z, 1.0f / sa.pz[c], sa.bel + (size_t)c * S,
+                       s_red, s_rows, U, L);
+  else
+    search_bounds<kSearchChildBlock>(m, sa, sa.bpa + (size_t)a * S, z, 1.0f / sa.pz[c],
+                                     sa.bel + (size_t)c * S, s_red, U, L);
   if (threadIdx.x == 0)
     search_new_node(sa, c, v * m.A + a, (float)sa.count[c] / (float)sa.n, z, sa.depth[v] + 1, U,
                     L);
@@ -3649,16 +3725,31 @@ __device__ void search_update_node(const DevModel &m, const SearchArgs &sa, int 
     const int a = lane;
     const float r = sa.rb[(size_t)v * A + a];
     float su = 0.f, sl = 0.f;
-    for (int i = 0; i < n; ++i) {
-      const int c = cb + a * n + i;
-      if (!sa.valid[c]) continue;
-      const float w = sa.w[c];
-      su = fmaf(w, ld_coherent(sa.U + c), su);
-      sl = fmaf(w, ld_coherent(sa.L + c), sl);
-      const float h = g * w * ld_coherent(sa.H + c);
-      if (h > hq) {
-        hq = h;
-        eq = __hip_atomic_load(sa.E + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // four children's fields at a time, read together (an absent child's are
+    // read and not used): a level of the climb waits for memory once
+    for (int i0 = 0; i0 < n; i0 += 4) {
+      int ok[4], e[4];
+      float w[4], u[4], l[4], h[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int c = cb + a * n + min(i0 + i, n - 1);
+        ok[i] = sa.valid[c];
+        w[i] = sa.w[c];
+        u[i] = ld_coherent(sa.U + c);
+        l[i] = ld_coherent(sa.L + c);
+        h[i] = ld_coherent(sa.H + c);
+        e[i] = __hip_atomic_load(sa.E + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (i0 + i >= n || !ok[i]) continue;
+        su = fmaf(w[i], u[i], su);
+        sl = fmaf(w[i], l[i], sl);
+        const float hc = g * w[i] * h[i];
+        if (hc > hq) {
+          hq = hc;
+          eq = e[i];
+        }
       }
     }
     uq = fmaf(g, su, r);
@@ -3718,11 +3809,13 @@ __global__ void k_search_update(DevModel m, SearchArgs sa) {
   }
   int p = v, cb = base;
   while (p >= 0) {
+    // the next level's node, on its way during this one
+    const int pq = p == root ? -1 : sa.parent[p];
+    const int pn = pq >= 0 ? pq / m.A : -1;
+    const int cn = pn >= 0 ? sa.cbase[pn] : 0;
     search_update_node(m, sa, p, cb);
-    if (p == root) break;
-    const int pq = sa.parent[p];
-    p = pq >= 0 ? pq / m.A : -1;
-    if (p >= 0) cb = sa.cbase[p];
+    p = pn;
+    cb = cn;
   }
   if (lane == 0)
     sa.ctl[kCtlSelect] = __hip_atomic_load(sa.E + root, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -3806,9 +3899,9 @@ __global__ __launch_bounds__(kBlock) void k_search_reroot(DevModel m, SearchArgs
   float p = 0.f;
   for (int t = tid; t < S; t += kBlock) {
     const uint32_t sg = sa.sig[t];
-    const int ly = fdiv(t, W, rW), lx = t - ly * W;
-    const float bt = t == m.goal ? bgoal : band[(ly + 1) * BW + lx + 1];
-    const float bp = predict_cell_v(band, BW, ly, lx, sg, sl, s_stay, bt);
+    const int pos = band_pos(t, rW, BW);
+    const float bt = t == m.goal ? bgoal : band[pos];
+    const float bp = predict_cell_v(band, BW, pos, sg, sl, s_stay, bt);
     bpl[t] = bp;
     p = fmaf(wall_lik(m.flip, zw, sig_wall(sg)) * lm_lik(m.lm_p, zl, sig_lm(sg)), bp, p);
   }
@@ -3946,9 +4039,9 @@ __global__ __launch_bounds__(kBlock) void k_pbvi_predict(DevModel m, PbviArgs pa
   float h0 = 0.f;
   for (int t = tid; t < S; t += kBlock) {
     const uint32_t sg = pa.sig[t];
-    const int ly = fdiv(t, W, rW), lx = t - ly * W;
-    const float bt = t == m.goal ? bgoal : band[(ly + 1) * BW + lx + 1];
-    const float bp = predict_cell_v(band, BW, ly, lx, sg, sl, s_stay, bt);
+    const int pos = band_pos(t, rW, BW);
+    const float bt = t == m.goal ? bgoal : band[pos];
+    const float bp = predict_cell_v(band, BW, pos, sg, sl, s_stay, bt);
     if (!EXPAND) {
       out[t] = bp;
     } else {
@@ -4234,8 +4327,7 @@ __global__ __launch_bounds__(kBlock) void k_pbvi_backup(DevModel m, PbviArgs pa,
       gsum = fmaf(c * lam0, gy[sidx[zw]], gsum);
       if (isl) gsum = fmaf(c * rho, gy[sidx[16 * lm + zw]], gsum);
     }
-    const int ly = fdiv(y, W, rW), lx = y - ly * W;
-    band[(ly + 1) * BW + lx + 1] = gsum;
+    band[band_pos(y, rW, BW)] = gsum;
   }
   __syncthreads();
   const float *bb = pa.pts + (size_t)b * S;
@@ -4246,8 +4338,7 @@ __global__ __launch_bounds__(kBlock) void k_pbvi_backup(DevModel m, PbviArgs pa,
     const uint32_t sg = pa.sig[x];
     float v = 0.f;
     if (sg & kSigFree) {
-      const int ly = fdiv(x, W, rW), lx = x - ly * W;
-      const float *c = band + (ly + 1) * BW + lx + 1;
+      const float *c = band + band_pos(x, rW, BW);
       const float r = m.R[(size_t)x * A + a];
       float e;
       if (sg & kSigGoal) {
