@@ -154,8 +154,9 @@ int32_t qv_belief_update_noalloc(const qv_model *m, int32_t batch, const float *
  *   Q_k(s,a) = R(s,a) + gamma * sum_s' T(s,a,s') V_k(s'),
  *   V_{k+1}(s) = max_a Q_k(s,a),  (blocked cells: Q = V = 0),
  * in FP32, with the residual r_k = max_s |V_{k+1}(s) - V_k(s)| formed in
- * FP64.  All sweeps run in one launch (a grid barrier between sweeps), so the
- * host waits once.  Stops after the first sweep with r_k = 0 or
+ * FP64.  Several sweeps run per launch (a map of at most 48 x 50 cells: all of
+ * them); the host reads the residuals after a group of launches, and sweeps
+ * past the last one leave no trace.  Stops after the first sweep with r_k = 0 or
  * r_k <= tol * max(1, max_s |V_{k+1}(s)|), or after max_sweeps sweeps.
  * Q: [S*A] FP32 output, Q_k of the last sweep.  Synchronous: on return
  * *residual_out (host) and *sweeps_out (host) hold r_k and k. */
