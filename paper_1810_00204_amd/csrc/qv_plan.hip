@@ -2398,7 +2398,10 @@ __device__ void leaf_parent_item(const DevModel &m, const LevelArgs &lv, const T
       acc[kk][AM] += s[kk];
     }
   };
-  uint32_t ea = entry(j0), eb = entry(j0 + sd);
+  // (a lane without a chunk takes the band's first cell: position 0 is never
+  // written where the map's first band has no free cell)
+  const uint32_t idle = (uint32_t)(y0 * W);
+  uint32_t ea = mine ? entry(j0) : idle, eb = mine ? entry(j0 + sd) : idle;
   float qa[AM], qb[AM];
   load_q_row<AM, QV>(lv, A, (int)(ea & kSortCell), qa);
   for (int j = j0; j < j1; j += sd) {
