@@ -280,7 +280,9 @@ namespace qv {
 //  * beliefs stay unnormalised, u_t = b_t U_t with U_t = sum u_t, rescaled by
 //    an exact power of two, and the bands are double-buffered (DB): a step
 //    reads one band, writes the other and has one barrier.  (Without room
-//    for two bands, DB = false: one band and a second barrier.)
+//    for two bands, DB = false: one band and a second barrier.)  A subnormal
+//    U_t (an observation of probability below 1e-38) takes a pass of its own
+//    over the band, so that the next step again has all its bits.
 //  * the reverse step is one pass over the cells: gather beta_{t-1} and the
 //    slip sums from band v_t, the flip sums from gamma_{t-1}, and v_{t-1}
 //    into the other band.  A failed move reads the cell itself: blocked and
@@ -367,11 +369,16 @@ __device__ __forceinline__ float filter_sum_waves(const float *p, bool small) {
          (((c.x + c.y) + (c.z + c.w)) + ((d.x + d.y) + (d.z + d.w)));
 }
 
-// The exact power of two that brings U into [1, 2) (1 for U = 0, infinite or
-// NaN, and where the power would not be a normal number).
-__device__ __forceinline__ float filter_scale(float U) {
-  const uint32_t e = (__float_as_uint(U) >> 23) & 0xFFu;
-  return (e >= 1u && e <= 253u) ? __uint_as_float((254u - e) << 23) : 1.f;
+// A step sees the sum U before it as U 2^-k in [1, 2), k = filter_exp(U) (U = 0,
+// infinite or NaN: any k).  Below -126, U is subnormal and 2^-k may not be a
+// float: the band is lifted by 2^23 first, which takes kFLift off k.
+constexpr int kFLift = 23;
+__device__ __forceinline__ int filter_exp(float U) {
+  return min(__builtin_amdgcn_frexp_expf(U) - 1, 126);
+}
+__device__ __forceinline__ float filter_scaled(float U) { return ldexpf(U, -filter_exp(U)); }
+__device__ __forceinline__ float filter_scale(int k) {
+  return __int_as_float((127 - (k < -126 ? k + kFLift : k)) << 23);
 }
 
 // Workgroup barrier for LDS alone: stores to global memory stay in flight
@@ -602,8 +609,10 @@ __global__ __launch_bounds__(kFMaxBlock) void k_filter(DevModel m, FilterArgs fa
       fill(0.f);
       __syncthreads();
       float *x = band0, *y = band1;
+      const int kb = tb == 0 ? 0 : __builtin_amdgcn_readfirstlane(filter_exp(u_at(tb - 1)));
       {
         const bool strips = tb != 0;
+        const float lift = kb < -126 ? 0x1p23f : 1.f;
         const float *src = strips ? ckpt + (size_t)sg * SL : b0;
         float *dst = grad && (!whole || tlast == 0) ? segb : nullptr;
         int o = pos + 1;
@@ -617,6 +626,7 @@ __global__ __launch_bounds__(kFMaxBlock) void k_filter(DevModel m, FilterArgs fa
             v = strips ? (src + (size_t)r * NT)[tid]
                        : src[fa.along_x ? i1 * m.W + j0 + r : (j0 + r) * m.W + i1];
           if (dst) (dst + (size_t)r * NT)[tid] = v;
+          v *= lift;
           if (!PLAIN && (info[r] & kFiGoal)) {
             gown = v;
             v = 0.f;
@@ -625,7 +635,7 @@ __global__ __launch_bounds__(kFMaxBlock) void k_filter(DevModel m, FilterArgs fa
         }
       }
       __syncthreads();
-      float s = tb == 0 ? 1.f : filter_scale(u_at(tb - 1));
+      float s = filter_scale(kb);
       int az = az_at(tb);
       int tk = fa.k;   // next step whose belief starts a segment
       for (int t = tb + 1; t <= t1; ++t) {
@@ -652,18 +662,26 @@ __global__ __launch_bounds__(kFMaxBlock) void k_filter(DevModel m, FilterArgs fa
           if (j == kFChunk - 1 || t == fa.T)
             for (int l = lane; l <= j; l += kWave) usum[i - j + l] = sh.u[l];
         }
-        s = filter_scale(U);
+        s = filter_scale(filter_exp(U));
+        if (__builtin_amdgcn_readfirstlane(__float_as_int(U)) - 1u < 0x7FFFFFu) {   // subnormal, rare: a pass over the band, own cells
+          if (act) {
+#pragma unroll 1
+            for (int r = 0, o = pos + P + 1; r < R; ++r, o += P) y[o] *= 0x1p23f;
+          }
+          gown *= 0x1p23f;
+          lds_barrier();
+        }
         float *o = x;
         x = y;
         y = o;
       }
       if (whole) {
-        // NLL = -sum log(U_t / (s_{t-1} U_{t-1})), in FP64
+        // NLL = -sum log(U_t / U_{t-1} as step t saw it), in FP64
         __syncthreads();
         double nll = 0.0;
         for (int t = 1 + tid; t <= fa.T; t += NT) {
           const float up = t > 1 ? usum[t - 2] : 1.f;
-          nll -= log((double)usum[t - 1] / ((double)up * (double)filter_scale(up)));
+          nll -= log((double)usum[t - 1] / (double)filter_scaled(up));
         }
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) nll += __shfl_xor(nll, o, kWave);
@@ -692,7 +710,7 @@ __global__ __launch_bounds__(kFMaxBlock) void k_filter(DevModel m, FilterArgs fa
       for (int i = 0; i < 5; ++i) gm[i] = 0.f;
       {
         // v_{t1} from beta_{t1}, and gamma_{t1}
-        const float ie = Up * filter_scale(Up) / U;   // 1 / eta_t
+        const float ie = filter_scaled(Up) / U;   // 1 / eta_t
         const uint32_t zl = (uint32_t)(z >> 4);
         const float *lk = sh.lik[zl ? 1 : 0][z & 15];
         const float *ut = segb + (size_t)(t1 - t0) * SL;
@@ -726,7 +744,7 @@ __global__ __launch_bounds__(kFMaxBlock) void k_filter(DevModel m, FilterArgs fa
         float w[9];
 #pragma unroll
         for (int q = 0; q < 9; ++q) w[q] = slip_at(a, q / 3 - 1, q % 3 - 1);
-        const float ie = Upp * filter_scale(Upp) / Up;   // 1 / eta_{t-1}
+        const float ie = filter_scaled(Upp) / Up;   // 1 / eta_{t-1}
         const uint32_t zl = (uint32_t)(zn >> 4);
         const float *lk = sh.lik[zl ? 1 : 0][zn & 15];
         float gn[5];
