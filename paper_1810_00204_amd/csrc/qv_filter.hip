@@ -298,7 +298,7 @@ namespace qv {
 constexpr int kFMaxBlock = 1024;
 constexpr int kFWaves = kFMaxBlock / kWave;
 constexpr int kFGrad = 85;   // 81 slip entries (A*9 used) + 4 flip entries
-constexpr int kFSums = 14;   // reverse step: 9 slip sums, gamma by wall bit (4), gamma
+constexpr int kFSums = 14;   // reverse step: 9 slip sums, gamma by wall bit's rarer reading (4), gamma
 constexpr int kFChunk = 256;   // steps whose inputs and sums are held in LDS
 constexpr int kFLik = 33;    // likelihood row: wall reading, the same on a landmark, blocked
 
@@ -461,6 +461,15 @@ __global__ __launch_bounds__(kFMaxBlock) void k_filter(DevModel m, FilterArgs fa
   float *ckpt = fa.ckpt + (size_t)blockIdx.x * fa.nseg * SL;
   float *segb = fa.seg + (size_t)blockIdx.x * (fa.k + 1) * SL;
   float *usum = fa.usum + (size_t)blockIdx.x * fa.T;
+
+  // Flip sums: per wall bit gamma is summed over the cells with the rarer
+  // reading (misread, or with f_j > 1/2 rightly read: bits of `rare`); the other
+  // reading has the rest.  The other way round, the rare one would be a
+  // difference of two sums, with their rounding and not its own.
+  uint32_t rare = 0u;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) rare |= sh.flip[i] > 0.5f ? 1u << i : 0u;
+  rare = __builtin_amdgcn_readfirstlane(rare);
 
   // slip weight of the move by d2 along and d1 across the strips: lane
   // 3 a + d1 + 1 of register d2 + 1 holds it
@@ -705,13 +714,13 @@ __global__ __launch_bounds__(kFMaxBlock) void k_filter(DevModel m, FilterArgs fa
       az = __builtin_amdgcn_readfirstlane(az_at(t1 - 1));
       int a = az & 255, z = az >> 8;
       float U = u_at(t1 - 1), Up = t1 > 1 ? u_at(t1 - 2) : 1.f;
-      float gs[9], gm[5];   // slip sums; gamma by wall bit and in all
+      float gs[9], gm[5];   // slip sums; gamma by wall bit's rarer reading and in all
 #pragma unroll
       for (int i = 0; i < 5; ++i) gm[i] = 0.f;
       {
         // v_{t1} from beta_{t1}, and gamma_{t1}
         const float ie = filter_scaled(Up) / U;   // 1 / eta_t
-        const uint32_t zl = (uint32_t)(z >> 4);
+        const uint32_t zl = (uint32_t)(z >> 4), zx = ((uint32_t)z ^ rare) << 10;
         const float *lk = sh.lik[zl ? 1 : 0][z & 15];
         const float *ut = segb + (size_t)(t1 - t0) * SL;
         int o = pos + 1;
@@ -724,7 +733,7 @@ __global__ __launch_bounds__(kFMaxBlock) void k_filter(DevModel m, FilterArgs fa
             x[o] = filter_lik<PLAIN>(lk, info[r], zl) * beta[r] * ie;
             const float ga = (ut + (size_t)r * NT)[tid] * beta[r];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) gm[i] += ((info[r] >> (10 + i)) & 1u) ? ga : 0.f;
+            for (int i = 0; i < 4; ++i) gm[i] += (((info[r] ^ zx) >> (10 + i)) & 1u) ? ga : 0.f;
             gm[4] += ga;
           }
         }
@@ -745,7 +754,7 @@ __global__ __launch_bounds__(kFMaxBlock) void k_filter(DevModel m, FilterArgs fa
 #pragma unroll
         for (int q = 0; q < 9; ++q) w[q] = slip_at(a, q / 3 - 1, q % 3 - 1);
         const float ie = filter_scaled(Upp) / Up;   // 1 / eta_{t-1}
-        const uint32_t zl = (uint32_t)(zn >> 4);
+        const uint32_t zl = (uint32_t)(zn >> 4), zx = ((uint32_t)zn ^ rare) << 10;
         const float *lk = sh.lik[zl ? 1 : 0][zn & 15];
         float gn[5];
 #pragma unroll
@@ -780,7 +789,7 @@ __global__ __launch_bounds__(kFMaxBlock) void k_filter(DevModel m, FilterArgs fa
             beta[r] = acc;
             const float ga = ub * acc;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) gn[i] += ((info[r] >> (10 + i)) & 1u) ? ga : 0.f;
+            for (int i = 0; i < 4; ++i) gn[i] += (((info[r] ^ zx) >> (10 + i)) & 1u) ? ga : 0.f;
             gn[4] += ga;
             if constexpr (DB) {
               const float v = filter_lik<PLAIN>(lk, info[r], zl) * acc * ie;
@@ -817,9 +826,9 @@ __global__ __launch_bounds__(kFMaxBlock) void k_filter(DevModel m, FilterArgs fa
           } else {
             const int i = tid - 9;
             const float all = filter_sum_waves(p + 13 * kFWaves, small);
-            const double on = (double)v / (double)U, off = ((double)all - (double)v) / (double)U;
-            sh.mis[i] += ((z >> i) & 1) ? off : on;
-            sh.ok[i] += ((z >> i) & 1) ? on : off;
+            const double few = (double)v / (double)U, rest = ((double)all - (double)v) / (double)U;
+            sh.mis[i] += ((rare >> i) & 1) ? rest : few;
+            sh.ok[i] += ((rare >> i) & 1) ? few : rest;
           }
         }
 #pragma unroll
