@@ -818,15 +818,17 @@ __global__ __launch_bounds__(kFMaxBlock) void k_filter(DevModel m, FilterArgs fa
         }
         if (tid < 13) {
           const float *p = &sh.gpart[t & 1][0][0];
-          const float v = filter_sum_waves(p + tid * kFWaves, small);
+          const double v = filter_sum_waves(p + tid * kFWaves, small);
+          const double all = filter_sum_waves(p + 13 * kFWaves, small);
+          // <beta_t, b_t> = all / U_t is 1 but for the steps' roundings, which
+          // would add up over the run: it is divided out of every step's terms
           if (tid < 9) {
             const int k = fa.along_x ? tid % 3 * 3 + tid / 3 : tid;
             // b_{t-1} = u_{t-1} / U_{t-1} (the start belief itself at t = 1)
-            sh.g[a * 9 + k] -= t > 1 ? (double)v / (double)Up : (double)v;
+            sh.g[a * 9 + k] -= v * (double)U / (t > 1 ? (double)Up * all : all);
           } else {
             const int i = tid - 9;
-            const float all = filter_sum_waves(p + 13 * kFWaves, small);
-            const double few = (double)v / (double)U, rest = ((double)all - (double)v) / (double)U;
+            const double few = v / all, rest = (all - v) / all;
             sh.mis[i] += ((rare >> i) & 1) ? rest : few;
             sh.ok[i] += ((rare >> i) & 1) ? few : rest;
           }
