@@ -339,15 +339,19 @@ __device__ __forceinline__ void keep_packed(uint32_t &v) { asm volatile("" : "+v
 __device__ __forceinline__ void keep_running(int &v) { asm volatile("" : "+v"(v)); }
 
 struct FilterShared {
+  // (the two read as 4-vectors come first, aligned)
+  alignas(16) float upart[2][kFWaves];          // per-wavefront sums of u_t, by step parity
+  alignas(16) float gpart[2][kFSums][kFWaves];  // per-wavefront reverse sums, by step parity
   float slip[81], flip[4];
   float lik[2][16][kFLik];          // [a landmark id observed][zw][entry]
-  float upart[2][kFWaves];          // per-wavefront sums of u_t, by step parity
-  float gpart[2][kFSums][kFWaves];  // per-wavefront reverse sums, by step parity
   double g[81], mis[4], ok[4];
   double red[kFWaves];
   int32_t az[kFChunk];              // action + 256 observation of a chunk of steps
   float u[kFChunk];                 // U of a chunk of steps
 };
+static_assert(offsetof(FilterShared, upart) % 16 == 0 && offsetof(FilterShared, gpart) % 16 == 0 &&
+                  kFWaves % 4 == 0,
+              "rows read as 4-vectors");
 
 // O(z|.) of a cell from the step's likelihood row (lk, zl uniform).
 template <bool PLAIN>
@@ -393,7 +397,7 @@ __device__ __forceinline__ void lds_barrier() {
 template <int R, bool DB, bool PLAIN>
 __global__ __launch_bounds__(kFMaxBlock) void k_filter(DevModel m, FilterArgs fa) {
   extern __shared__ float smem[];
-  __shared__ __attribute__((aligned(16))) FilterShared sh;
+  __shared__ FilterShared sh;
   const int A = m.A, n1 = fa.n1, n2 = fa.n2, P = n1 + 2;
   const int NT = blockDim.x, tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int band_floats = (fa.ng * R + 2) * P;
