@@ -3225,18 +3225,20 @@ __global__ void k_prep_landmarks_batch(BatchPrep bp) {
 // a query with 9 actions, leaf scoring and backup (k_leaf);
 // PHASE 2: the last level of a query with at most 8 actions, per (parent,
 // band) over all actions (k_leaf_parent).
-// An item of phases 0 and 1 is a (parent, band) with all its actions (PP; a
-// last level with 9 actions and PP = false: one action), so a band is loaded
-// once; results are bitwise those of an item per action.  Workgroups take
+// An item of phases 0 and 1 is a (parent, band) with all its actions (PP), so
+// a band is loaded once, or, at a last level with 9 actions and at levels of
+// few items, one action of it; results are bitwise the same.  Workgroups take
 // `chunk` items at a time from the queue until it runs dry; every workgroup
 // leaves after one failed take.
 // An item is a few microseconds of work, so what it waits for ahead of its
 // band counts as much: the next take is in flight while the current items are
-// worked on, the search for the item's query waits for memory once, the
-// descriptors come by scalar loads, and nothing goes through generic pointers.
-// Statistics at four workgroups a CU (4 registers spilled) 1.1 ms, at two
-// (189 registers) 1.4.  Measured, 256 queries of sides 32..256 (phases 0, 1,
-// 2): 2.5, 2.6, 3.2 -> 1.0, 0.7, 2.9 ms; the batch 7.92 -> 4.35 ms.
+// worked on (until four visits per workgroup are left: 16 queries of sides
+// 32..128 took 191 us with it to the end, 173 so), the search for the item's
+// query waits for memory once, the descriptors come by scalar loads, and
+// nothing goes through generic pointers.  Statistics at four workgroups a CU
+// (4 registers spilled) 1.1 ms, at two (189 registers) 1.4.  Measured, 256
+// queries of sides 32..256 (phases 0, 1, 2): 2.5, 2.6, 3.2 -> 1.0, 0.7, 2.9 ms;
+// the batch 7.92 -> 4.35 ms.
 // (phase 2 runs k_leaf_parent's 512-thread form, so a query's results equal
 // those of its single-query plan bit for bit)
 template <int PHASE, int APAD, bool PP>
@@ -3252,7 +3254,10 @@ __global__ __launch_bounds__(PHASE == 2 ? kLeafBlock : kBlock, PHASE == 2 && APA
     const int i0 = s_item;
     if (i0 >= bl.total) break;
     int next = 0;
-    if (threadIdx.x == 0) {
+    // (not near the end of the queue: an item held by a busy workgroup waits
+    // while others run dry)
+    const bool ahead = i0 + 4 * (int)gridDim.x * bl.chunk < bl.total;
+    if (threadIdx.x == 0 && ahead) {
       // (an address that the compiler does not know to be uniform: else it
       // makes one add for the wavefront and waits for it here)
       int z = 0;
@@ -3289,7 +3294,7 @@ __global__ __launch_bounds__(PHASE == 2 ? kLeafBlock : kBlock, PHASE == 2 && APA
     // the wait is spelt out: the compiler leaves that of the barrier at the top
     // out on this way round the loop, and wavefronts would part with
     // different items
-    if (threadIdx.x == 0) s_item = next;
+    if (threadIdx.x == 0) s_item = ahead ? next : atomicAdd(bl.queue, bl.chunk);
     wait_lds();
   }
 }
