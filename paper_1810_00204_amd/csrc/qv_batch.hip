@@ -36,7 +36,8 @@ struct qv_batch {
   std::vector<qv_model> models;
   std::vector<int> D;
   int tile_cells = 0, chunk = 1;
-  bool pp = true;               // phases 0, 1 by (parent, band) items over all actions
+  // phases 0, 1 of a level by (parent, band) items over all actions
+  std::vector<char> pp;
   // layout of the current shape
   std::vector<PlanLayout> lay;
   std::vector<size_t> qoff;
@@ -72,6 +73,13 @@ void drop_graphs(qv_batch *b) {
   b->graphs_ready = false;
 }
 
+// A level with fewer (parent, band) pairs than two per CU leaves CUs idle with
+// an item each, and takes an item per action.  Measured, 16 queries of sides
+// 32..128, 8 actions, D = 2: 173 us by action, 191 by parent; 64 queries of
+// sides 32..256, 4 actions (about 1500 pairs): 369 and 303; 700 of sides 8..12:
+// 536 and 485.
+constexpr long long kParentItems = 512;
+
 // Workspace layout for bands of about tile_cells cells; false if a query's
 // tree or a level's item count leaves this build's index ranges.
 bool layout(qv_batch *b, int tile_cells, bool commit) {
@@ -100,17 +108,24 @@ bool layout(qv_batch *b, int tile_cells, bool commit) {
   size_t lds0 = 0, lds1 = 0, lds2 = 0;
   int apad1 = 4, apad2 = 4;
   // (parent, band) items over all actions where every band fits a thread's
-  // kParentCells; wider bands take one item per action
-  bool pp = true;
-  for (int q = 0; q < nq; ++q) {
-    const qv_model &m = b->models[q];
-    if ((long long)band_rows(m.W, m.H, tile_cells) * m.W > kParentCells * kBlock) pp = false;
-  }
+  // kParentCells and the level has at least kParentItems of them; else an item
+  // per action
+  bool ppfit = true;
+  std::vector<long long> parents(b->dmax, 0);   // (parent, band) pairs of a level
   for (int q = 0; q < nq; ++q) {
     const qv_model &m = b->models[q];
     const int th = band_rows(m.W, m.H, tile_cells);
+    if ((long long)th * m.W > kParentCells * kBlock) ppfit = false;
     if (!plan_layout_impl(&m, b->D[q], b->n, 0, &lay[q], th)) return false;
     qoff[q] = take(lay[q].pub.total_bytes);
+    for (int d = 0; d + 1 < b->D[q]; ++d)
+      parents[d] += lay[q].pub.level_slots[d] * lay[q].pub.tiles;
+  }
+  std::vector<char> pp(b->dmax);
+  for (int d = 0; d < b->dmax; ++d) pp[d] = ppfit && parents[d] >= kParentItems;
+  for (int q = 0; q < nq; ++q) {
+    const qv_model &m = b->models[q];
+    const int th = band_rows(m.W, m.H, tile_cells);
     const qv_tree_layout &T = lay[q].pub;
     // the last level of a query with A <= 8 runs (parent, leaf band) items in
     // phase 2; every other level runs (parent, band) items (a last level of 9
@@ -122,7 +137,7 @@ bool layout(qv_batch *b, int tile_cells, bool commit) {
         long long items = 0;
         const bool banded = d + 1 < b->D[q] || (d + 1 == b->D[q] && !lp);
         if (ph < 2 && banded)
-          items = T.level_slots[d] * T.tiles * (pp && d + 1 < b->D[q] ? 1 : m.A);
+          items = T.level_slots[d] * T.tiles * (pp[d] && d + 1 < b->D[q] ? 1 : m.A);
         else if (ph == 2 && d + 1 == b->D[q] && lp)
           items = T.level_slots[d] * lay[q].leaf_tiles;
         tot[ph * b->dmax + d] += items;
@@ -140,7 +155,7 @@ bool layout(qv_batch *b, int tile_cells, bool commit) {
     lb += (m.L + 255) / 256;
     if (pb > (1LL << 30)) return false;
     lds0 = std::max(lds0, band_lds_bytes(m.W, th) + (size_t)16 * kBlock * 4);
-    if (pp) lds0 = std::max(lds0, stats_parent_lds_bytes(m.W, th, m.L));
+    if (ppfit) lds0 = std::max(lds0, stats_parent_lds_bytes(m.W, th, m.L));
     if (lp) {
       const int am = m.A <= 4 ? 4 : 8;
       apad2 = std::max(apad2, am);
@@ -204,9 +219,9 @@ bool size_grids(qv_batch *b) {
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return false;
   for (int ph = 0; ph < 3; ++ph) {
-    const int occ = batch_level_occupancy(ph, b->apad[ph], b->lds[ph], b->pp);
-    if (occ <= 0) return false;
     for (int d = 0; d < b->dmax; ++d) {
+      const int occ = batch_level_occupancy(ph, b->apad[ph], b->lds[ph], b->pp[d]);
+      if (occ <= 0) return false;
       const long long visits =
           ((long long)b->totals[ph * b->dmax + d] + b->chunk - 1) / b->chunk;
       b->grid[ph][d] = (int)std::min<long long>(visits, (long long)cus * occ);
@@ -358,7 +373,7 @@ hipError_t enqueue_level(const qv_batch *b, char *ws, int d, hipStream_t st, boo
   }
   for (int ph = 0; ph < 3; ++ph) {
     e = launch_batch_level(level_args(b, ws, d, ph), ph, b->apad[ph], b->lds[ph],
-                           b->grid[ph][d], b->pp, st, timed);
+                           b->grid[ph][d], b->pp[d], st, timed);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
