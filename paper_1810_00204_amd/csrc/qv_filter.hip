@@ -305,6 +305,7 @@ constexpr int kFLik = 33;    // likelihood row: wall reading, the same on a land
 struct FilterArgs {
   int ntraj, T, k, nseg, G;
   int n1, n2, ng;     // cells across and along the strips, strips along
+  int pitch;          // floats from one row of a band to the next, n1 + 2 at least
   int along_x;         // strips run along x (lanes along y)
   const float *theta, *phi;
   const float *b0;
@@ -403,7 +404,7 @@ template <int R, bool DB, bool PLAIN>
 __global__ __launch_bounds__(kFMaxBlock) void k_filter(DevModel m, FilterArgs fa) {
   extern __shared__ float smem[];
   __shared__ FilterShared sh;
-  const int A = m.A, n1 = fa.n1, n2 = fa.n2, P = n1 + 2;
+  const int A = m.A, n1 = fa.n1, n2 = fa.n2, P = fa.pitch;
   const int NT = blockDim.x, tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int band_floats = (fa.ng * R + 2) * P;
   float *band0 = smem, *band1 = DB ? smem + band_floats : smem;
@@ -921,7 +922,7 @@ bool filter_supported(const qv_model *m) { return filter_lds_bytes(m) <= 150 * 1
 // How a grid is cut into strips, and how many trajectories run at once.  It
 // depends on the grid alone (and so do all sums), except for G.
 struct FilterPlan {
-  int n1, n2, along_x, rr, ng, threads, G;
+  int n1, n2, along_x, rr, ng, pitch, threads, G;
   bool db;
   size_t lds;
 };
@@ -951,9 +952,16 @@ static FilterPlan filter_plan(int W, int H, int A, int ntraj) {
       p.threads = waves * kWave;
     }
   }
-  const size_t band = (size_t)(p.ng * p.rr + 2) * (p.n1 + 2) * sizeof(float);
   const size_t rest = (size_t)A * 256 * sizeof(float);
   const size_t room = 160 * 1024 - sizeof(FilterShared);
+  auto band_bytes = [&](int pitch) { return (size_t)(p.ng * p.rr + 2) * pitch * sizeof(float); };
+  // On narrow grids a wavefront holds many strips; where their starts would
+  // all fall on one or two banks of the LDS, rows are a float apart more (2000x2, 64
+  // runs x 20 steps, NLL: 121 us without, 86 with).
+  p.pitch = p.n1 + 2;
+  if (p.n1 < kWave && p.rr * p.pitch % 32 == 0 && 2 * band_bytes(p.pitch + 1) + rest <= room)
+    ++p.pitch;
+  const size_t band = band_bytes(p.pitch);
   p.db = 2 * band + rest <= room;
   p.lds = (p.db ? 2 : 1) * band + rest;
   int dev = 0, cus = 0;
@@ -1048,6 +1056,7 @@ hipError_t launch_filter(const DevModel &m, const float *theta, const float *phi
   fa.n1 = p.n1;
   fa.n2 = p.n2;
   fa.ng = p.ng;
+  fa.pitch = p.pitch;
   fa.along_x = p.along_x;
   fa.theta = theta;
   fa.phi = phi;
