@@ -1,6 +1,7 @@
-"""The filter kernel's strips: every strip length, both directions, remainders
-of strips and of wavefronts, one band and two, a goal and landmarks in each,
-and more steps than one chunk of inputs, against the FP64 oracle.
+"""The filter kernel's strips: strips of 1, 2, 4, 12, 16 and 22 cells, both
+directions, remainders of strips and of wavefronts, one band and two, with and
+without a goal and landmarks, and more steps than one chunk of inputs, against
+the FP64 oracle.
 
 Tolerances as for the other filter sets (test_gpu_filter_adjoint.py): 2e-5
 relative on the NLL; 1e-4 on each part and entry of the gradient, 5e-4 on
