@@ -927,13 +927,19 @@ struct FilterPlan {
   size_t lds;
 };
 
+// Bytes that the stored beliefs of several workgroups a CU may take.  Measured,
+// 4096 runs on 24x24: 2000 steps, every 10th stored, 36 ms in 804 MiB, 49 in
+// 515, 82 in 259 and 162 in 123 (one a CU); 200 steps, every 14th, 3.6 ms in
+// 116 MiB.
+constexpr size_t kFilterStore = (size_t)512 << 20;
+
 // Strip length: the one of least estimated time of a step on the busiest
 // SIMD, in cycles: each of its wavefronts takes about 800 for the step itself
 // (inputs, reduction, barrier) and 110 per cell, so a small grid is better
 // cut into few wavefronts of longer strips.  Measured on 24x24, 8 runs x 200
 // steps, NLL: 9 wavefronts of 1 cell 343 us, 3 of 4 cells 208 us.  The longest strips
 // spill registers and are taken only where nothing shorter covers the grid.
-static FilterPlan filter_plan(int W, int H, int A, int ntraj) {
+static FilterPlan filter_plan(int W, int H, int A, int ntraj, int T, int k) {
   FilterPlan p;
   p.along_x = W > H ? 1 : 0;
   p.n1 = p.along_x ? H : W;
@@ -971,7 +977,13 @@ static FilterPlan filter_plan(int W, int H, int A, int ntraj) {
     cus = 256;
   const int per = std::max<int>(1, std::min<int>(16 / (p.threads / kWave),
                                                  (int)(160 * 1024 / (p.lds + sizeof(FilterShared)))));
-  p.G = std::max(1, std::min(ntraj, cus * per));
+  // Several workgroups a CU as long as their stored beliefs take no more than
+  // one a CU would for the bare cells, or than kFilterStore.
+  const size_t nseg = (T + k - 1) / k;
+  const size_t each = (nseg + k + 1) * p.rr * p.threads * 4 + (size_t)T * 4;
+  const size_t bare = (nseg + k + 2) * W * H * 4 + (size_t)(T + 1) * 4;
+  const size_t limit = std::max((size_t)std::min(ntraj, cus) * bare, kFilterStore);
+  p.G = std::max(1, (int)std::min<size_t>(std::min(ntraj, cus * per), limit / each));
   return p;
 }
 
@@ -1002,7 +1014,7 @@ static FilterWs filter_layout(const FilterPlan &p, int W, int H, int A, int ntra
 }
 
 size_t filter_ws(const qv_model *m, int ntraj, int T, int k) {
-  const FilterPlan p = filter_plan(m->W, m->H, m->A, ntraj);
+  const FilterPlan p = filter_plan(m->W, m->H, m->A, ntraj, T, k);
   return filter_layout(p, m->W, m->H, m->A, ntraj, T, k).total;
 }
 
@@ -1042,7 +1054,7 @@ hipError_t launch_filter(const DevModel &m, const float *theta, const float *phi
                          int T, const float *b0, int b0_per_traj, const int32_t *acts,
                          const int32_t *obs, int k, float *nll, float *g_slip, float *g_flip,
                          char *ws, hipStream_t st) {
-  const FilterPlan p = filter_plan(m.W, m.H, m.A, ntraj);
+  const FilterPlan p = filter_plan(m.W, m.H, m.A, ntraj, T, k);
   const FilterWs w = filter_layout(p, m.W, m.H, m.A, ntraj, T, k);
   uint32_t *sig = (uint32_t *)(ws + w.sig);
   hipError_t e = launch_prep(m, sig, (float *)(ws + w.staytab), (int32_t *)(ws + w.err), st);
