@@ -54,7 +54,7 @@ def test_fib_forms_match_oracle(W, H, A, L, dense, goal, launches, monkeypatch):
         R = torch.empty(m.S * A + 1, dtype=torch.float32, device="cuda")
         R[1:].copy_(torch.as_tensor(prob.R.reshape(-1)))
         m.c.R = R.data_ptr() + 4
-    n = 40   # past one chunk of sweeps
+    n = 40
     al = torch.empty(m.S * A, dtype=torch.float32, device="cuda")
     ws = torch.empty(B.qv_fib_workspace_bytes(m, n), dtype=torch.uint8, device="cuda")
     st, res, sw = B.qv_fib_iterate(m, 0.0, n, al, ws)
