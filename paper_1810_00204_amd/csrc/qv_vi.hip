@@ -34,6 +34,9 @@ constexpr int kMaxCoopGrid = 4096;   // workgroups of a one-launch solve at most
 // workgroups of a sweep launch at most: four per CU; more would only add
 // residual slots for every workgroup to read
 constexpr int kSweepGrid = 1024;
+// FIB's are a wavefront per action; of two, twice as many (512x512, 2 actions,
+// dense rows, a sweep: 38 us, 33 so)
+constexpr int kFibGrid = 2048;
 constexpr int kMaxWaves = 16;   // wavefronts of a sweep workgroup at most
 
 // ---------------------------------------------------------------------------
@@ -1415,7 +1418,7 @@ static hipError_t run_fib_am(const DevModel &m, const SweepWs &w, FibCells fc, f
   // as many workgroups as are resident at once: they take the groups in turn,
   // and a part-filled second round would cost as much as the first (512x512,
   // a sweep: 1024 workgroups 34.9 us, 768 32.2, the resident 512 25.7)
-  const int g = std::min(want, std::min(kSweepGrid, resident_grid(
+  const int g = std::min(want, std::min(kFibGrid, resident_grid(
       reinterpret_cast<const void *>(&k_fib_sweep<AM, NJ, FULL>), threads, 0)));
   e = sweep_chunks(
       w, g,
@@ -1468,7 +1471,9 @@ hipError_t run_fib(const DevModel &m, float tol, int max_sweeps, float *alpha,
   const FibCells fc = fib_cells(ws + sweep_ws(m.S, m.A, vals, max_sweeps), m.S, nullptr);
   hipError_t e = sweep_setup(m, w, vals, st);
   if (e != hipSuccess) return e;
-  if (op == 1) {
+  // (with one action there is no maximum to take, and the FIB equation is the
+  // blind one; 300x300, 40 sweeps: 1.06 ms by the FIB kernels, 0.40 so)
+  if (op == 1 || m.A == 1) {
     if (m.A <= 4) return run_blind_am<4>(m, w, alpha, residual, sweeps, st);
     if (m.A <= 8) return run_blind_am<8>(m, w, alpha, residual, sweeps, st);
     return run_blind_am<9>(m, w, alpha, residual, sweeps, st);
