@@ -25,7 +25,8 @@ class Planner:
         nb = B.qv_plan_workspace_bytes(self.m, self.D, self.n, flags)
         if nb == 0:
             raise B.QvError(B.QV_ERR_UNSUPPORTED, "qv_plan_workspace_bytes")
-        self.ws = torch.empty(nb, dtype=torch.uint8, device=device)
+        # (zeros: a plan writes no values of absent nodes, and tree() returns them)
+        self.ws = torch.zeros(nb, dtype=torch.uint8, device=device)
         st, self.layout = B.qv_plan_layout(self.m, self.D, self.n, flags)
         B.check(st, "qv_plan_layout")
         self.action = torch.zeros(1, dtype=torch.int32, device=device)
