@@ -292,7 +292,7 @@ namespace qv {
 // Stored beliefs are in strip order [row of strip][thread], so their accesses
 // are coalesced whatever the strips' direction.  Every sum runs in a fixed
 // order that depends on the grid alone.  Measured, NLL + gradient of 1024
-// runs x 50 steps on 128x128: 11.6 -> 3.6 ms (one thread per cell,
+// runs x 50 steps on 128x128: 11.6 -> 3.4 ms (one thread per cell,
 // two band reads and three barriers a step, before).
 // ===========================================================================
 constexpr int kFMaxBlock = 1024;
@@ -937,8 +937,10 @@ constexpr size_t kFilterStore = (size_t)512 << 20;
 // SIMD, in cycles: each of its wavefronts takes about 800 for the step itself
 // (inputs, reduction, barrier) and 110 per cell, so a small grid is better
 // cut into few wavefronts of longer strips.  Measured on 24x24, 8 runs x 200
-// steps, NLL: 9 wavefronts of 1 cell 343 us, 3 of 4 cells 208 us.  The longest strips
-// spill registers and are taken only where nothing shorter covers the grid.
+// steps, NLL: 9 wavefronts of 1 cell 343 us, 3 of 4 cells 208 us.  From 8 cells on
+// a strip spills registers (9 at 8, 31 at 12, 57 at 16, 91 at 22 cells, up to
+// six more with landmarks or a goal); those of 22 count double, so that they are
+// taken only where nothing shorter covers the grid.
 static FilterPlan filter_plan(int W, int H, int A, int ntraj, int T, int k) {
   FilterPlan p;
   p.along_x = W > H ? 1 : 0;

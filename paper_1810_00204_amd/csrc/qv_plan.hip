@@ -475,7 +475,7 @@ __device__ __forceinline__ void load_band(const DevModel &m, const uint32_t *sig
   const int nc = (W + kWave - 1) / kWave;         // pieces of a row (1 where q > 1)
   const int lr = q > 1 ? lane / W : 0;
   // piece u: rows q (u / nc) on, cells 64 (u mod nc) on; the division as a
-  // product: exact for u nc < 2^19, and a band has at most 2^11 pieces, nc 2^8
+  // product: exact for u nc < 2^19, and a band has at most 2^11 pieces, nc 2^5
   const int inv = __builtin_amdgcn_readfirstlane((int)((float)(1 << 20) / (float)nc)) + 1;
   const int nu = (rows + q - 1) / q * nc;
   const int lo = max(0, y0 - 1) * W, hi = min(m.H, y0 + th + 1) * W;   // cells on the grid
@@ -3237,8 +3237,8 @@ __global__ void k_prep_landmarks_batch(BatchPrep bp) {
 // query waits for memory once, the descriptors come by scalar loads, and
 // nothing goes through generic pointers.  Statistics at four workgroups a CU
 // (4 registers spilled) 1.1 ms, at two (189 registers) 1.4.  Measured, 256
-// queries of sides 32..256 (phases 0, 1, 2): 2.5, 2.6, 3.2 -> 1.0, 0.7, 2.9 ms;
-// the batch 7.92 -> 4.35 ms.
+// queries of sides 32..256 (phases 0, 1, 2): 2.5, 2.6, 3.2 -> 1.0, 0.7, 2.6 ms;
+// the batch 7.67 -> 3.85 ms.
 // (phase 2 runs k_leaf_parent's 512-thread form, so a query's results equal
 // those of its single-query plan bit for bit)
 template <int PHASE, int APAD, bool PP>

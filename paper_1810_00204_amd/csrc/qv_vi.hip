@@ -651,8 +651,8 @@ __global__ __launch_bounds__(kBlock) void k_fib_scatter(DevModel m, const uint32
 // action's value from the rows its moves need, held in registers.  Bound by
 // the vector ALU and the latency of the row loads; one thread per cell with
 // all rows and actions took 160 VGPRs, three wavefronts per SIMD, and left
-// both exposed.  Measured, 512x512, a sweep: 123 us before (16 terms of nine moves for
-// every cell, and the residual's atomics), 24.8 now.
+// both exposed.  Measured, 512x512, 8 actions of three moves, a sweep: 123 us before
+// (16 terms of nine moves for every cell, and the residual's atomics), 24.8 now.
 template <int AM>
 struct FibShared {
   static constexpr int Q = AM / 4, E = AM % 4;   // a row: Q 4-vectors and E (0 or 1) values
@@ -1201,19 +1201,19 @@ static hipError_t sweep_setup(const DevModel &m, const SweepWs &w, long long val
   return hipGetLastError();
 }
 
-// Grids up to this many cells take the one-launch form; larger ones the
-// per-sweep launches.  Measured on MI355X (a sweep, one-launch vs
-// per-sweep): 4096 cells, value iteration 12.3 vs 15.3 us; 262144 cells, value
-// iteration 20.4 vs 16.4, blind bound 162 vs 46 -- at that size the coherent loads of the gathered values (past
-// the L2) cost more than the launches they save.
+// Blind bound: grids up to this many cells take the one-launch form; larger
+// ones the per-sweep launches.  Measured (a sweep, one launch vs per sweep):
+// 262144 cells 162 vs 46 us -- at that size the coherent loads of the gathered
+// values (past the L2) cost more than the launches they save; 40 sweeps of
+// 16384 cells 750 us in one launch, of 16512 by sweep 665.
 constexpr long long kCoopMaxCells = 16384;
 // FIB, by cells times actions, a solve, one launch / per sweep: 64x64x8 1.11 /
 // 1.31 ms, 100x40x9 2.50 / 3.24, 512x30x8 3.28 / 2.83, 128x128x8 2.62 / 2.38.
 constexpr long long kFibCoopMaxValues = 65536;
 
 // Workgroups of a cooperative launch of `kernel`: at most `want`, and no
-// more than can be resident at once; 0 for the per-sweep form: a grid of
-// more than kCoopMaxCells cells, no cooperative launch on this device, or
+// more than can be resident at once; 0 for the per-sweep form: a `size`
+// (cells, or values) above `most`, no cooperative launch on this device, or
 // QVTS_SWEEP_LAUNCHES=1.  QVTS_SWEEP_COOP=1 takes the one-launch form at
 // any size.
 static int coop_grid(const void *kernel, int threads, size_t lds, int want, long long size,
