@@ -1208,8 +1208,11 @@ static hipError_t sweep_setup(const DevModel &m, const SweepWs &w, long long val
 // 16384 cells 750 us in one launch, of 16512 by sweep 665.
 constexpr long long kCoopMaxCells = 16384;
 // FIB, by cells times actions, a solve, one launch / per sweep: 64x64x8 1.11 /
-// 1.31 ms, 100x40x9 2.50 / 3.24, 512x30x8 3.28 / 2.83, 128x128x8 2.62 / 2.38.
-constexpr long long kFibCoopMaxValues = 65536;
+// 1.31 ms, 100x40x9 2.50 / 3.24, 512x30x8 3.28 / 2.83, 128x128x8 2.62 / 2.38;
+// and by cells, since the barrier waits for a workgroup per 64 of them: 40
+// sweeps of 110x110, 2 and 4 actions, 0.61 / 0.61 and 0.64 / 0.61 ms, of 140x140
+// 0.75 / 0.63 and 0.81 / 0.63.
+constexpr long long kFibCoopMaxValues = 65536, kFibCoopMaxCells = 12288;
 
 // Workgroups of a cooperative launch of `kernel`: at most `want`, and no
 // more than can be resident at once; 0 for the per-sweep form: a `size`
@@ -1401,7 +1404,9 @@ static hipError_t run_fib_am(const DevModel &m, const SweepWs &w, FibCells fc, f
   const int threads = m.A * kWave;
   const int want = std::max(1, (fc.nfree + kWave - 1) / kWave);
   const void *coop = reinterpret_cast<const void *>(&k_fib_coop<AM, NJ, FULL>);
-  const int G = coop_grid(coop, threads, 0, want, (long long)m.S * m.A, kFibCoopMaxValues);
+  const long long size = (long long)m.S * std::max<long long>(
+      m.A, m.S > kFibCoopMaxCells ? kFibCoopMaxValues : 0);
+  const int G = coop_grid(coop, threads, 0, want, size, kFibCoopMaxValues);
   if (G > 0) {
     DevModel mm = m;
     const float *stay = w.staytab;
